@@ -13,8 +13,8 @@
 // K and V tiles are loaded from HBM into LDS without passing through
 // registers; V^T fragments come from transposed LDS reads.
 //
-// f32 path: a plain VALU kernel (one thread per query row) used for float32
-// inputs, where accuracy rather than speed is the point.
+// f32 path: the same structure on the float32 MFMA (v_mfma_f32_32x32x2_f32),
+// every operand, probability and sum in float32.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -394,94 +394,235 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_bf16(AttnArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// f32 VALU kernel: one thread per query row, 64 rows per work item.
+// f32 MFMA kernel: one work item = 64 query rows, four waves = two blocks of
+// 32 queries x two halves of the keys.
+//
+// Bound by the matrix cores (v_mfma_f32_32x32x2_f32, 256 flop per cycle and
+// CU).  As in the bf16 kernel every lane owns one query row: S^T = K Q^T, and
+// the 32 probabilities of a key block feed O^T = V^T P^T straight from
+// registers (MFMA step j multiplies the two keys the half-waves hold in
+// element j).  The wave of half w takes the 32-key block 2 jt + w of every
+// 64-key tile, so that a query row's chain of MFMAs over the segment is half
+// as long (a 2048-key row takes 56 us on one SIMD instead of 112, against
+// 126 us for the whole 4K-token, 12-head, D = 64 call) and its end does not
+// leave the chip idle; the two halves' (max, sum, O) meet in LDS at the end.
+// A V row is read DB = D / 32 consecutive floats per lane: MFMA row m of
+// accumulator e holds head-dim column DB m + e.
+// Measured (B = 1, N = 4096, H = 12, D = 64, patterns (2048, 1), (4096, 2)):
+// the call took 2417 us with one thread per query on the vector ALUs and
+// takes 218 us here (88 Tflop/s; 109 at N = 16384, where the last items weigh
+// less); two accumulators for S instead of one chain measured 226 us.
 // ---------------------------------------------------------------------------
-constexpr int kBM32 = 64;
-constexpr int kBN32 = 16;
+constexpr int kBM32 = 64;  // query rows per work item
+constexpr int kBN32 = 64;  // keys per K/V tile, one 32-key block per half
+
+// LDS layout of float32 rows: D/4 16-byte slots per row, logical slot c of
+// row k at slot c ^ swz(k), so that 16 consecutive rows at one slot fall into
+// sixteen bank groups (see TileLayout).
+template <int D>
+struct TileLayoutF32 {
+  static constexpr int kSlots = D / 4;
+  static constexpr int kRowBytes = D * 4;
+  __device__ static constexpr int swz(int row) { return D == 32 ? (row >> 1) & 7 : row & 15; }
+  __device__ static int offset(int row, int slot) { return row * kRowBytes + ((slot ^ swz(row)) << 4); }
+};
 
 template <int D>
-__global__ __launch_bounds__(kBM32) void attn_fwd_f32(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) float ks[kBN32][D];
-  __shared__ __attribute__((aligned(16))) float vs[kBN32][D];
+struct SmemF32 {
+  __attribute__((aligned(16))) float k[2][kBN32 * D];  // double-buffered K tiles
+  __attribute__((aligned(16))) float v[2][kBN32 * D];  // double-buffered V tiles
+};
+
+template <int D, bool kBufferLoads>
+__global__ __launch_bounds__(kThreads) void attn_fwd_f32(AttnArgs a) {
+  constexpr int BN = kBN32;
+  constexpr int KC = D / 8;   // 16-byte slices of a row per half-wave
+  constexpr int DB = D / 32;  // 32-row accumulators of O^T
+  using TL = TileLayoutF32<D>;
+  typedef float vrow __attribute__((ext_vector_type(DB)));
+  constexpr int kLoadsPerWave = BN * TL::kSlots / 64 / (kThreads / 64);
+  __shared__ SmemF32<D> sm;
+
   Item it;
   if (!decode_item(a, __builtin_amdgcn_workgroup_id_x(), kBM32, it)) return;
   const PatArgs& P = a.pat[it.pi];
-  const float* __restrict__ qg = static_cast<const float*>(a.q);
-  const float* __restrict__ kg = static_cast<const float*>(a.k);
-  const float* __restrict__ vg = static_cast<const float*>(a.v);
   const int tid = __builtin_amdgcn_workitem_id_x();
+  const int lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qb = wv & 1, kh = wv >> 1;  // query block and key half of this wave
+  const int qr = lane & 31, hi = lane >> 5;
   const int L = it.L;
   const int q0 = it.tq * kBM32;
   const int qend = min(q0 + kBM32, L);
-  const int t = q0 + tid;
-  const bool valid = t < L;
+  const int wq_lo = q0 + qb * 32;
+  const int tq_row = wq_lo + qr;
+  const bool q_valid = tq_row < L;
+  const int64_t row_step = it.rstride * D;
+  const float c = a.scale_log2;
 
-  float qv[D], o[D];
+  // Q^T operand: elements [8c + 4hi, +4) of this lane's query (rows past the
+  // segment's end repeat its last row; their results are not stored).
+  f32x4 qreg[KC];
   {
-    const float* qp = qg + (it.row0 + (int64_t)min(t, L - 1) * it.rstride) * D;
+    const float* qp = static_cast<const float*>(a.q) + (it.row0 + (int64_t)min(tq_row, L - 1) * it.rstride) * D + 4 * hi;
 #pragma unroll
-    for (int d = 0; d < D; d += 4) {
-      const f32x4 x = *reinterpret_cast<const f32x4*>(qp + d);
-      qv[d] = x[0]; qv[d + 1] = x[1]; qv[d + 2] = x[2]; qv[d + 3] = x[3];
-      o[d] = o[d + 1] = o[d + 2] = o[d + 3] = 0.0f;
-    }
+    for (int x = 0; x < KC; ++x) qreg[x] = *reinterpret_cast<const f32x4*>(qp + 8 * x);
   }
-  float m_run = kNegBig, l_run = 0.0f;
-  const int kv_end = a.causal ? qend : L;
-  const int lim = a.causal ? t : L - 1;
-  for (int k0 = 0; k0 < kv_end; k0 += kBN32) {
-    __syncthreads();
-    for (int task = tid; task < kBN32 * D / 4; task += kBM32) {
-      const int key = task / (D / 4);
-      const int dc = (task % (D / 4)) * 4;
-      const int tk = k0 + key;
-      f32x4 xk = f32x4{0, 0, 0, 0}, xv = f32x4{0, 0, 0, 0};
-      if (tk < L) {
-        const int64_t off = (it.row0 + (int64_t)tk * it.rstride) * D + dc;
-        xk = *reinterpret_cast<const f32x4*>(kg + off);
-        xv = *reinterpret_cast<const f32x4*>(vg + off);
+
+  int lrow[kLoadsPerWave], lslot[kLoadsPerWave];
+#pragma unroll
+  for (int i = 0; i < kLoadsPerWave; ++i) {
+    const int s = 64 * (wv * kLoadsPerWave + i) + lane;
+    lrow[i] = s / TL::kSlots;
+    lslot[i] = (s % TL::kSlots) ^ TL::swz(lrow[i]);
+  }
+  const float* kbase = static_cast<const float*>(a.k) + it.row0 * D;
+  const float* vbase = static_cast<const float*>(a.v) + it.row0 * D;
+  auto load_tile = [&](int jt, int buf) {
+    const int k0 = jt * BN;
+    char* kl = reinterpret_cast<char*>(&sm.k[buf][0]);
+    char* vl = reinterpret_cast<char*>(&sm.v[buf][0]);
+    if constexpr (kBufferLoads) {
+      // rows past the segment's last kept row arrive as zeros
+      const uint64_t row_bytes = static_cast<uint64_t>(row_step) * 4;
+      const uint64_t valid = static_cast<uint64_t>(L - k0) * row_bytes;
+      const int nrec = static_cast<int>(valid < 0x7fffffffull ? valid : 0x7fffffffull);
+      const __amdgpu_buffer_rsrc_t ksrc =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(kbase + row_step * k0), 0, nrec, kBufferFlags);
+      const __amdgpu_buffer_rsrc_t vsrc =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(vbase + row_step * k0), 0, nrec, kBufferFlags);
+#pragma unroll
+      for (int i = 0; i < kLoadsPerWave; ++i) {
+        const int off = static_cast<int>(lrow[i] * row_bytes) + lslot[i] * 16;
+        const int lds_off = 1024 * (wv * kLoadsPerWave + i);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ksrc, (lds_void*)(kl + lds_off), 16, off, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(vsrc, (lds_void*)(vl + lds_off), 16, off, 0, 0, 0);
       }
-      *reinterpret_cast<f32x4*>(&ks[key][dc]) = xk;
-      *reinterpret_cast<f32x4*>(&vs[key][dc]) = xv;
+    } else {
+      // 64-bit addresses; rows past the segment's end re-read its last row
+#pragma unroll
+      for (int i = 0; i < kLoadsPerWave; ++i) {
+        const int64_t off = (int64_t)min(k0 + lrow[i], L - 1) * row_step + lslot[i] * 4;
+        const int lds_off = 1024 * (wv * kLoadsPerWave + i);
+        __builtin_amdgcn_global_load_lds(kbase + off, (lds_void*)(kl + lds_off), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(vbase + off, (lds_void*)(vl + lds_off), 16, 0, 0);
+      }
     }
+  };
+
+  const int kv_end = a.causal ? qend : L;
+  const int ntile = (kv_end + BN - 1) / BN;
+  const int lim = a.causal ? min(tq_row, L - 1) : L - 1;  // last visible key of this lane
+  // V read of this lane: key row 4hi (plus a constant), columns [DB qr, +DB).
+  const int vcol = DB * qr * 4;
+  const int vlane = (vcol & ~15) ^ (TL::swz(4 * hi) << 4);  // 16-byte slot, swizzled for rows 4hi + {0..3}
+  const int vsub = (vcol & 15) + 4 * hi * TL::kRowBytes;
+
+  f32x16 acc_o[DB];
+#pragma unroll
+  for (int e = 0; e < DB; ++e) acc_o[e] = f32x16{};
+  float m_run = kNegBig, l_run = 0.0f;  // running max (log2 units), this half-wave's share of the sum
+
+  load_tile(0, 0);
+  __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+  __syncthreads();
+  for (int jt = 0; jt < ntile; ++jt) {
+    const int cur = jt & 1;
+    if (jt + 1 < ntile) load_tile(jt + 1, cur ^ 1);
+    const char* kl = reinterpret_cast<const char*>(&sm.k[cur][0]) + kh * 32 * TL::kRowBytes;
+    const char* vl = reinterpret_cast<const char*>(&sm.v[cur][0]) + kh * 32 * TL::kRowBytes;
+    const int kb0 = jt * BN + kh * 32;  // first key of this wave's block
+    // Blocks entirely after this wave's queries or past the segment are skipped.
+    if (kb0 < L && !(a.causal && kb0 > wq_lo + 31)) {
+      f32x16 s = f32x16{};
+#pragma unroll
+      for (int x = 0; x < KC; ++x) {
+        const f32x4 kf = *reinterpret_cast<const f32x4*>(kl + TL::offset(qr, 2 * x + hi));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qreg[x][e], s, 0, 0, 0);
+      }
+      if ((a.causal && kb0 + 31 > wq_lo) || kb0 + 32 > L) {
+        int base = kb0 + 4 * hi - lim;
+        asm volatile("" : "+v"(base));  // compares stay inside the branch
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+          if (base + 8 * (j >> 2) + (j & 3) > 0) s[j] = -INFINITY;
+      }
+      float mx = s[0];
+#pragma unroll
+      for (int j = 1; j < 16; ++j) mx = fmaxf(mx, s[j]);
+      const float m_new = fmaxf(m_run, fmaxf(mx, other_half(mx)) * c);
+      if (__any(m_new > m_run)) {
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int e = 0; e < DB; ++e)
+#pragma unroll
+          for (int j = 0; j < 16; ++j) acc_o[e][j] *= alpha;
+      }
+      float lp[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        s[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[j], c, -m_run));
+        lp[j & 3] += s[j];
+      }
+      l_run += (lp[0] + lp[1]) + (lp[2] + lp[3]);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int row = 8 * (j >> 2) + (j & 3);  // plus 4hi: the key of element j
+        const vrow vf = *reinterpret_cast<const vrow*>(vl + row * TL::kRowBytes + vsub + (vlane ^ (TL::swz(row) << 4)));
+#pragma unroll
+        for (int e = 0; e < DB; ++e) {
+          float ve;
+          if constexpr (DB == 1) ve = vf[0];
+          else ve = vf[e];
+          acc_o[e] = __builtin_amdgcn_mfma_f32_32x32x2f32(ve, s[j], acc_o[e], 0, 0, 0);
+        }
+      }
+    }
+    // the next tile has landed and every wave is done with this one
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();
-    float s[kBN32];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < kBN32; ++j) {
-      float acc = 0.0f;
-#pragma unroll
-      for (int d = 0; d < D; ++d) acc = fmaf(qv[d], ks[j][d], acc);
-      s[j] = (k0 + j <= lim) ? acc : -INFINITY;
-      mx = fmaxf(mx, s[j]);
-    }
-    const float m_new = fmaxf(m_run, mx * a.scale_log2);
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-    m_run = m_new;
-    float psum = 0.0f;
-#pragma unroll
-    for (int j = 0; j < kBN32; ++j) {
-      s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], a.scale_log2, -m_new));
-      psum += s[j];
-    }
-    l_run = fmaf(l_run, alpha, psum);
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      float acc = o[d] * alpha;
-#pragma unroll
-      for (int j = 0; j < kBN32; ++j) acc = fmaf(s[j], vs[j][d], acc);
-      o[d] = acc;
-    }
   }
-  if (!valid) return;
-  const float inv = 1.0f / l_run;
-  const int64_t wrow = (int64_t)it.unit * P.lmax + t;
+
+  // Merge the two key halves through LDS (the tiles are no longer read).
+  float* stg = &sm.k[0][0] + qb * (16 * DB + 2) * 64 + lane;
+  if (kh == 1) {
+    stg[0] = m_run;
+    stg[64] = l_run;
+#pragma unroll
+    for (int e = 0; e < DB; ++e)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) stg[(2 + 16 * e + j) * 64] = acc_o[e][j];
+  }
+  __syncthreads();
+  if (kh == 1) return;
+  const float m1 = stg[0];
+  const float m_tot = fmaxf(m_run, m1);
+  const float w0 = __builtin_amdgcn_exp2f(m_run - m_tot), w1 = __builtin_amdgcn_exp2f(m1 - m_tot);
+  const float l_half = l_run * w0 + stg[64] * w1;
+  const float l_tot = l_half + other_half(l_half);
+  const float inv = 1.0f / l_tot;
+#pragma unroll
+  for (int e = 0; e < DB; ++e)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) acc_o[e][j] = (acc_o[e][j] * w0 + stg[(2 + 16 * e + j) * 64] * w1) * inv;
+  if (!q_valid) return;
+  const int64_t wrow = (int64_t)it.unit * P.lmax + tq_row;
   float* orow = reinterpret_cast<float*>(a.ws + P.o_off) + wrow * D;
 #pragma unroll
-  for (int d = 0; d < D; d += 4)
-    *reinterpret_cast<f32x4*>(orow + d) = f32x4{o[d] * inv, o[d + 1] * inv, o[d + 2] * inv, o[d + 3] * inv};
+  for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+    for (int x = 0; x < DB; ++x) {
+      f32x4 o;  // columns DB (8jj + 4hi) + 4x + {0..3}
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = acc_o[(4 * x + e) % DB][4 * jj + (4 * x + e) / DB];
+      *reinterpret_cast<f32x4*>(orow + DB * (8 * jj + 4 * hi) + 4 * x) = o;
+    }
   // float32 rows need no scale: the record's scale is 1
-  reinterpret_cast<f32x2*>(a.ws + P.lse_off)[wrow] = f32x2{(m_run + __builtin_amdgcn_logf(l_run)) * kLn2, 1.0f};
+  if (hi == 0)
+    reinterpret_cast<f32x2*>(a.ws + P.lse_off)[wrow] = f32x2{(m_tot + __builtin_amdgcn_logf(l_tot)) * kLn2, 1.0f};
 }
 
 }  // namespace
@@ -545,9 +686,18 @@ hipError_t launch_attention(const Plan& plan, const void* q, const void* k, cons
     }
   } else {
     switch (plan.D) {
-      case 32: hipLaunchKernelGGL(attn_fwd_f32<32>, grid, dim3(kBM32), 0, stream, a); break;
-      case 64: hipLaunchKernelGGL(attn_fwd_f32<64>, grid, dim3(kBM32), 0, stream, a); break;
-      case 128: hipLaunchKernelGGL(attn_fwd_f32<128>, grid, dim3(kBM32), 0, stream, a); break;
+      case 32:
+        if (plan.offsets32) hipLaunchKernelGGL((attn_fwd_f32<32, true>), grid, dim3(kThreads), 0, stream, a);
+        else hipLaunchKernelGGL((attn_fwd_f32<32, false>), grid, dim3(kThreads), 0, stream, a);
+        break;
+      case 64:
+        if (plan.offsets32) hipLaunchKernelGGL((attn_fwd_f32<64, true>), grid, dim3(kThreads), 0, stream, a);
+        else hipLaunchKernelGGL((attn_fwd_f32<64, false>), grid, dim3(kThreads), 0, stream, a);
+        break;
+      case 128:
+        if (plan.offsets32) hipLaunchKernelGGL((attn_fwd_f32<128, true>), grid, dim3(kThreads), 0, stream, a);
+        else hipLaunchKernelGGL((attn_fwd_f32<128, false>), grid, dim3(kThreads), 0, stream, a);
+        break;
       default: return hipErrorInvalidValue;
     }
   }
