@@ -19,7 +19,8 @@
 //              known), and dQ^T += K^T dS^T;
 //   bwd_dkdv   per (pattern, segment, 128-key tile): each lane owns a key;
 //              over the query tiles that see it, S = Q K^T and dP - delta =
-//              dO V^T, then dV^T += dO^T P and dK^T += Q^T dS;
+//              dO V^T, then dV^T += dO^T P and dK^T += Q^T dS (bwd_dkdv_wide
+//              for D = 128);
 //   bwd_sum    per row: the compact per-pattern gradients of every pattern
 //              that keeps the row, summed and rounded to bf16.
 // The compact per-pattern gradients are fp16 rows scaled by a power of two
@@ -59,27 +60,12 @@ struct BwdArgs {
 };
 
 constexpr int kThreadsB = 256;  // four waves
-// Head-dim columns of dq (or dk, dv) one work item accumulates: all of them up
-// to D = 64; at D = 128 each item is run twice, once per 64-column half (the
-// scores and dP are recomputed, the accumulators fit in registers).
+// Columns of a compact gradient row that share one scale (kGradChunk of the
+// plan, or the whole row if it is shorter), and scales per row.
 template <int D>
-constexpr int kCols = D <= 64 ? D : 64;
-// Scales per compact gradient row: one per item's column range.
+constexpr int kCols = D <= kGradChunk ? D : static_cast<int>(kGradChunk);
 template <int D>
 constexpr int kChunks = D / kCols<D>;
-// Launch index of a split work item: the two halves of an item take two
-// consecutive slots of the same XCD.  Returns the item's launch index and sets
-// `half`.
-template <int D>
-__device__ inline int split_index(int bid, int& half) {
-  if constexpr (kCols<D> == D) {
-    half = 0;
-    return bid;
-  } else {
-    half = (bid >> 3) & 1;
-    return ((bid >> 4) << 3) | (bid & 7);
-  }
-}
 constexpr int kTileB = 128;     // rows (queries for dq, keys for dk/dv) per work item
 constexpr int kStepB = 64;      // rows per LDS tile of the other operand
 
@@ -87,7 +73,7 @@ template <int D>
 struct SmemTiles {
   __attribute__((aligned(16))) u16 a[2][kStepB * D];  // K (dq) or Q (dk/dv) tiles
   __attribute__((aligned(16))) u16 b[2][kStepB * D];  // V (dq) or dO (dk/dv) tiles
-  __attribute__((aligned(16))) float s0[2][kStepB];   // -lse*log2(e) of the query rows (dk/dv)
+  __attribute__((aligned(16))) float s0[2][kStepB];   // -lse/scale of the query rows (dk/dv)
   __attribute__((aligned(16))) float s1[2][kStepB];   // -delta of the query rows (dk/dv)
 };
 
@@ -107,13 +93,13 @@ __device__ inline void load_rowslices(const u16* row, int hi, float mul, bool ze
     }
 }
 
-// Loads of one tile of kStepB kept rows (row stride row_step elements, base at
+// Loads of one tile of kRows kept rows (row stride row_step elements, base at
 // the tile's first row, `valid` rows before the segment's end) straight into
 // LDS: load i of wave wv fills 16-byte LDS slots [64 (wv*kLoads + i), +64).
-template <int D>
+template <int D, int kRows = kStepB>
 struct TileLoader {
   using TL = TileLayout<D>;
-  static constexpr int kLoads = kStepB * TL::kSlots / 64 / (kThreadsB / 64);
+  static constexpr int kLoads = kRows * TL::kSlots / 64 / (kThreadsB / 64);
   int lrow[kLoads], lslot[kLoads];
   __device__ void init(int wv, int lane) {
 #pragma unroll
@@ -188,20 +174,22 @@ __global__ __launch_bounds__(kThreadsB) void bwd_delta(DeltaArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// bwd_dq: one work item = 128 query rows of one sparsified segment.
+// bwd_dq: one work item = 128 query rows of one sparsified segment, all head-dim
+// columns.  Two or three waves per SIMD; the scores start from zero and -lse
+// enters with the scale in one FMA (at D = 128 the 16 registers this frees
+// hold row slices in flight: 250 VGPRs).  D = 128, B = 1, N = 32768, H = 16,
+// patterns (2048, 1), (8192, 2), (32768, 4): 1095 us, against 1877 us when the
+// items ran once per 64-column half (40 instead of 24 MFMAs per block).
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
   constexpr int BN = kStepB;
-  constexpr int KC = D / 16, DB = kCols<D> / 32, SB = BN / 32;
+  constexpr int KC = D / 16, DB = D / 32, SB = BN / 32;
   using TL = TileLayout<D>;
   __shared__ SmemTiles<D> sm;
 
   Item it;
-  int half;
-  const int bid = split_index<D>(__builtin_amdgcn_workgroup_id_x(), half);
-  const int c0 = half * kCols<D>;  // first head-dim column this item accumulates
-  if (!decode_item(a, bid, kTileB, it)) return;
+  if (!decode_item(a, __builtin_amdgcn_workgroup_id_x(), kTileB, it)) return;
   const BwdPat& P = a.pat[it.pi];
   const int tid = __builtin_amdgcn_workitem_id_x();
   const int lane = tid & 63;
@@ -234,13 +222,11 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
   load_rowslices<KC>(static_cast<const u16*>(a.q) + qoff, hi, 1.0f, !q_valid, qreg);
   load_rowslices<KC>(static_cast<const u16*>(a.dout) + qoff, hi, 1.0f, !q_valid, doreg);
   const int64_t srow = ((int64_t)it.b * a.H + it.h) * a.N + it.p0 + (int64_t)qrow * P.r;
-  const float nl2 = a.nl2[srow], nd = a.nd[srow];
-  f32x16 vnl2, vnd;
+  const float nl = a.nl2[srow] * a.scale_log2;  // -lse in log2 units
+  const float nd = a.nd[srow];
+  f32x16 vnd;
 #pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    vnl2[j] = nl2;
-    vnd[j] = nd;
-  }
+  for (int j = 0; j < 16; ++j) vnd[j] = nd;
   f32x16 acc_dq[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) acc_dq[db] = f32x16{};
@@ -255,7 +241,7 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const int d = c0 + db * 32 + tr_d;
+      const int d = db * 32 + tr_d;
       vtr_off[db][t] = TL::offset(8 * t + 4 * hi + tr_r, d >> 3) + (d & 7) * 2;
     }
 
@@ -272,18 +258,26 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
       const uint32_t kaddr = lds_addr(kl);
       static_for<0, SB>([&](auto KB) {
         constexpr int kb = decltype(KB)::value;
-        // S'^T = K Q^T - lse/scale and (dP - delta)^T = V dO^T - delta
-        u32x4 kf[KC], vf[KC];
+        // S^T = K Q^T and (dP - delta)^T = V dO^T - delta; four pairs of row
+        // slices are in flight.
+        constexpr int PF = KC < 4 ? KC : 4;
+        u32x4 kf[PF], vf[PF];
+        auto read_pair = [&](int c) {
+          kf[c % PF] = *reinterpret_cast<const u32x4*>(kl + TL::offset(kb * 32 + qr, 2 * c + hi));
+          vf[c % PF] = *reinterpret_cast<const u32x4*>(vl + TL::offset(kb * 32 + qr, 2 * c + hi));
+        };
+#pragma unroll
+        for (int c = 0; c < PF; ++c) read_pair(c);
+        __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the MFMAs
+        f32x16 s = f32x16{}, dp = vnd;
 #pragma unroll
         for (int c = 0; c < KC; ++c) {
-          kf[c] = *reinterpret_cast<const u32x4*>(kl + TL::offset(kb * 32 + qr, 2 * c + hi));
-          vf[c] = *reinterpret_cast<const u32x4*>(vl + TL::offset(kb * 32 + qr, 2 * c + hi));
-        }
-        f32x16 s = vnl2, dp = vnd;
-#pragma unroll
-        for (int c = 0; c < KC; ++c) {
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[c]), qreg[c], s, 0, 0, 0);
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf[c]), doreg[c], dp, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[c % PF]), qreg[c], s, 0, 0, 0);
+          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf[c % PF]), doreg[c], dp, 0, 0, 0);
+          if (c + PF < KC) {
+            read_pair(c + PF);
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
         if (masked) {
           const int base = k0 + kb * 32 + 4 * hi - lim;
@@ -297,7 +291,7 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
         for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
           for (int e = 0; e < 8; ++e)
-            dsb[kk][e] = (__bf16)(__builtin_amdgcn_exp2f(s[8 * kk + e] * a.scale_log2) * dp[8 * kk + e]);
+            dsb[kk][e] = (__bf16)(__builtin_amdgcn_exp2f(__builtin_fmaf(s[8 * kk + e], a.scale_log2, nl)) * dp[8 * kk + e]);
         // K^T fragments through transposed reads (keys kb*32 + 16kk + 8t + 4hi + {0..3})
         u32x2 kt[2][DB][2];
         static_for<0, 2>([&](auto KK) {
@@ -325,27 +319,36 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
     __syncthreads();
   }
 
-  // dq = scale * acc over this item's columns, stored scaled (both half-waves
-  // hold parts of the row: the max is exchanged before any lane leaves).
-  float amax = 0.0f;
+  // dq = scale * acc, stored scaled per column chunk (both half-waves hold
+  // parts of the row: the max is exchanged before any lane leaves).
+  constexpr int CB = kCols<D> / 32;  // accumulators per chunk
+  float mul[kChunks<D>], rs[kChunks<D>];
 #pragma unroll
-  for (int db = 0; db < DB; ++db)
+  for (int ch = 0; ch < kChunks<D>; ++ch) {
+    float amax = 0.0f;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) amax = fmaxf(amax, fabsf(acc_dq[db][j]));
-  amax = fmaxf(amax, other_half(amax));
+    for (int db = ch * CB; db < (ch + 1) * CB; ++db)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) amax = fmaxf(amax, fabsf(acc_dq[db][j]));
+    amax = fmaxf(amax, other_half(amax));
+    row_scale(amax * a.scale, a.scale, mul[ch], rs[ch]);
+  }
   if (!q_valid) return;
-  float mul, rs;
-  row_scale(amax * a.scale, a.scale, mul, rs);
   const int64_t wrow = (int64_t)it.unit * P.lmax + tq_row;
   _Float16* orow = reinterpret_cast<_Float16*>(a.ws + P.dq_off) + wrow * D;
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
-      *reinterpret_cast<f16x4*>(orow + c0 + db * 32 + 8 * jj + 4 * hi) =
-          f16x4{(_Float16)(acc_dq[db][4 * jj] * mul), (_Float16)(acc_dq[db][4 * jj + 1] * mul),
-                (_Float16)(acc_dq[db][4 * jj + 2] * mul), (_Float16)(acc_dq[db][4 * jj + 3] * mul)};
-  if (hi == 0) reinterpret_cast<float*>(a.ws + P.dq_rec_off)[wrow * kChunks<D> + half] = rs;
+    for (int jj = 0; jj < 4; ++jj) {
+      const float m = mul[db / CB];
+      *reinterpret_cast<f16x4*>(orow + db * 32 + 8 * jj + 4 * hi) =
+          f16x4{(_Float16)(acc_dq[db][4 * jj] * m), (_Float16)(acc_dq[db][4 * jj + 1] * m),
+                (_Float16)(acc_dq[db][4 * jj + 2] * m), (_Float16)(acc_dq[db][4 * jj + 3] * m)};
+    }
+  if (hi == 0)
+#pragma unroll
+    for (int ch = 0; ch < kChunks<D>; ++ch)
+      reinterpret_cast<float*>(a.ws + P.dq_rec_off)[wrow * kChunks<D> + ch] = rs[ch];
 }
 
 // ---------------------------------------------------------------------------
@@ -354,15 +357,13 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
 template <int D>
 __global__ __launch_bounds__(kThreadsB) void bwd_dkdv(BwdArgs a) {
   constexpr int BQ = kStepB;
-  constexpr int KC = D / 16, DB = kCols<D> / 32, QB = BQ / 32;
+  constexpr int KC = D / 16, DB = D / 32, QB = BQ / 32;
+  static_assert(kChunks<D> == 1, "one scale per row");
   using TL = TileLayout<D>;
   __shared__ SmemTiles<D> sm;
 
   Item it;
-  int half;
-  const int bid = split_index<D>(__builtin_amdgcn_workgroup_id_x(), half);
-  const int c0 = half * kCols<D>;  // first head-dim column this item accumulates
-  if (!decode_item(a, bid, 0, it)) return;
+  if (!decode_item(a, __builtin_amdgcn_workgroup_id_x(), 0, it)) return;
   const BwdPat& P = a.pat[it.pi];
   const int kt_idx = P.ntiles - 1 - it.tq;  // longest (first) key tiles first
   const int L = it.L;
@@ -419,7 +420,7 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dkdv(BwdArgs a) {
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const int d = c0 + db * 32 + tr_d;
+      const int d = db * 32 + tr_d;
       vtr_off[db][t] = TL::offset(8 * t + 4 * hi + tr_r, d >> 3) + (d & 7) * 2;
     }
 
@@ -515,8 +516,8 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dkdv(BwdArgs a) {
     __syncthreads();
   }
 
-  // dk = scale * acc_dk and dv = acc_dv over this item's columns, stored
-  // scaled (the row maxima are exchanged before any lane leaves).
+  // dk = scale * acc_dk and dv = acc_dv, stored scaled (the row maxima are
+  // exchanged before any lane leaves).
   float amax_k = 0.0f, amax_v = 0.0f;
 #pragma unroll
   for (int db = 0; db < DB; ++db)
@@ -538,7 +539,7 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dkdv(BwdArgs a) {
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {
-      const int d = c0 + db * 32 + 8 * jj + 4 * hi;
+      const int d = db * 32 + 8 * jj + 4 * hi;
       *reinterpret_cast<f16x4*>(krow_out + d) =
           f16x4{(_Float16)(acc_dk[db][4 * jj] * mul_k), (_Float16)(acc_dk[db][4 * jj + 1] * mul_k),
                 (_Float16)(acc_dk[db][4 * jj + 2] * mul_k), (_Float16)(acc_dk[db][4 * jj + 3] * mul_k)};
@@ -547,9 +548,258 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dkdv(BwdArgs a) {
                 (_Float16)(acc_dv[db][4 * jj + 2] * mul_v), (_Float16)(acc_dv[db][4 * jj + 3] * mul_v)};
     }
   if (hi == 0) {
-    reinterpret_cast<float*>(a.ws + P.dk_rec_off)[wrow * kChunks<D> + half] = rs_k;
-    reinterpret_cast<float*>(a.ws + P.dv_rec_off)[wrow * kChunks<D> + half] = rs_v;
+    reinterpret_cast<float*>(a.ws + P.dk_rec_off)[wrow] = rs_k;
+    reinterpret_cast<float*>(a.ws + P.dv_rec_off)[wrow] = rs_v;
   }
+}
+
+// ---------------------------------------------------------------------------
+// bwd_dkdv_wide: dk/dv for D = 128, 128 key rows and all columns per item.
+//
+// bwd_dkdv's register budget does not fit here: the accumulators of 32 keys
+// and 128 columns alone are 128 registers, K and V operands 64, scores and dP
+// 32.  The V operands are therefore read from LDS (the item's 128 V rows stay
+// there; dP's B operand costs 8 more 16-byte reads per 32-query block, with
+// the LDS 39 % busy), and Q/dO tiles are 32 rows, so that two workgroups share
+// a CU (66 KB of LDS, 252 VGPRs, nothing spilled).  Bound by the matrix cores
+// and the softmax's vector work, which overlap only in part (MFMA 51 % busy).
+// At B = 1, N = 32768, H = 16, patterns (2048, 1), (8192, 2), (32768, 4):
+// 1574 us, against 2330 us when every item ran once per 64-column half and
+// formed the scores and dP twice (48 instead of 32 MFMAs per 32 x 32 block).
+// One wave per SIMD with 512 registers was not built further: the compiler
+// copies the operands it keeps in accumulation registers before every MFMA.
+// ---------------------------------------------------------------------------
+constexpr int kStepW = 32;  // query rows per LDS tile
+
+template <int D>
+struct SmemWide {
+  __attribute__((aligned(16))) u16 v[kTileB * D];     // the item's V rows
+  __attribute__((aligned(16))) u16 a[2][kStepW * D];  // Q tiles
+  __attribute__((aligned(16))) u16 b[2][kStepW * D];  // dO tiles
+  __attribute__((aligned(16))) float s0[2][kStepW];   // -lse/scale of the query rows
+  __attribute__((aligned(16))) float s1[2][kStepW];   // -delta of the query rows
+};
+
+template <int D>
+__global__ __launch_bounds__(kThreadsB, 2) void bwd_dkdv_wide(BwdArgs a) {
+  constexpr int BQ = kStepW;
+  constexpr int KC = D / 16, DB = D / 32;
+  using TL = TileLayout<D>;
+  __shared__ SmemWide<D> sm;
+
+  Item it;
+  if (!decode_item(a, __builtin_amdgcn_workgroup_id_x(), 0, it)) return;
+  const BwdPat& P = a.pat[it.pi];
+  const int kt_idx = P.ntiles - 1 - it.tq;  // longest (first) key tiles first
+  const int L = it.L;
+  const int kt0 = kt_idx * kTileB;
+  if (kt0 >= L) return;
+  const int tid = __builtin_amdgcn_workitem_id_x();
+  const int lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kr = lane & 31, hi = lane >> 5;
+  const int kw0 = kt0 + wv * 32;  // this wave's first key
+  const int tk_row = kw0 + kr;
+  const bool k_valid = tk_row < L;
+  const int krow = min(tk_row, L - 1);
+  const int64_t row_step = it.rstride * D;
+
+  TileLoader<D, BQ> ld;
+  ld.init(wv, lane);
+  const u16* qbase = static_cast<const u16*>(a.q) + it.row0 * D;
+  const u16* obase = static_cast<const u16*>(a.dout) + it.row0 * D;
+  const int64_t sbase = ((int64_t)it.b * a.H + it.h) * a.N + it.p0;
+  // Query tiles: every tile holding a query at or after the first key (causal).
+  const int qt_first = a.causal ? kt0 / BQ : 0;
+  const int qt_end = (L + BQ - 1) / BQ;
+  auto load_tile = [&](int qt, int buf) {
+    const int64_t o = row_step * BQ * qt;
+    ld.load(qbase + o, row_step, L - qt * BQ, reinterpret_cast<char*>(&sm.a[buf][0]), wv);
+    ld.load(obase + o, row_step, L - qt * BQ, reinterpret_cast<char*>(&sm.b[buf][0]), wv);
+    if (wv < 2 && lane < BQ) {
+      // the query rows' scalars: one 4-byte load per lane, rows r apart
+      const float* src = (wv == 0 ? a.nl2 : a.nd) + sbase + (int64_t)qt * BQ * P.r;
+      const uint64_t vb = (static_cast<uint64_t>(L - qt * BQ - 1) * P.r + 1) * 4;
+      const int nrec = static_cast<int>(vb < 0x7fffffffull ? vb : 0x7fffffffull);
+      const __amdgpu_buffer_rsrc_t rs =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(src), 0, nrec, kBufferFlags);
+      float* dst = wv == 0 ? &sm.s0[buf][0] : &sm.s1[buf][0];
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)dst, 4, lane * P.r * 4, 0, 0, 0);
+    }
+  };
+  load_tile(qt_first, 0);
+  {
+    // the item's V rows, 32 at a time (rows past the segment's end arrive as zeros)
+    const u16* vbase = static_cast<const u16*>(a.v) + it.row0 * D + row_step * kt0;
+#pragma unroll
+    for (int i = 0; i < kTileB / BQ; ++i)
+      ld.load(vbase + row_step * (i * BQ), row_step, L - kt0 - i * BQ, reinterpret_cast<char*>(&sm.v[i * BQ * D]), wv);
+  }
+
+  // K^T operand of this lane's key (as given).
+  const int64_t koff = (it.row0 + (int64_t)krow * it.rstride) * D;
+  bf16x8 kreg[KC];
+  load_rowslices<KC>(static_cast<const u16*>(a.k) + koff, hi, 1.0f, !k_valid, kreg);
+  f32x16 acc_dk[DB], acc_dv[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) acc_dk[db] = acc_dv[db] = f32x16{};
+  const int tr_r = (lane & 15) >> 2;
+  const int tr_d = ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
+  int toff[DB][2];
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int d = db * 32 + tr_d;
+      toff[db][t] = TL::offset(8 * t + 4 * hi + tr_r, d >> 3) + (d & 7) * 2;
+    }
+  const char* vl = reinterpret_cast<const char*>(&sm.v[wv * 32 * D]);
+
+  __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+  __syncthreads();
+  for (int qt = qt_first; qt < qt_end; ++qt) {
+    const int cur = (qt - qt_first) & 1;
+    const int q0 = qt * BQ;
+    if (qt + 1 < qt_end) load_tile(qt + 1, cur ^ 1);
+    const char* ql = reinterpret_cast<const char*>(&sm.a[cur][0]);
+    const char* ol = reinterpret_cast<const char*>(&sm.b[cur][0]);
+    // Tiles entirely before this wave's keys are skipped (causal).
+    if (!(a.causal && q0 + BQ - 1 < kw0)) {
+      const uint32_t qaddr = lds_addr(ql), oaddr = lds_addr(ol);
+      // C layout of S[q][key]: this lane's key, queries 8(j/4) + 4hi + j%4.
+      f32x16 s, dp;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(&sm.s0[cur][8 * i + 4 * hi]);
+        const f32x4 y = *reinterpret_cast<const f32x4*>(&sm.s1[cur][8 * i + 4 * hi]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s[4 * i + e] = x[e];
+          dp[4 * i + e] = y[e];
+        }
+      }
+      // S = Q K^T and dP - delta = dO V^T; PF steps' slices are in flight.
+      constexpr int PF = 2;
+      u32x4 qf[PF], of[PF], vf[PF];
+      auto read_step = [&](int c) {
+        const int off = TL::offset(kr, 2 * c + hi);
+        qf[c % PF] = *reinterpret_cast<const u32x4*>(ql + off);
+        of[c % PF] = *reinterpret_cast<const u32x4*>(ol + off);
+        vf[c % PF] = *reinterpret_cast<const u32x4*>(vl + off);
+      };
+#pragma unroll
+      for (int c = 0; c < PF; ++c) read_step(c);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int c = 0; c < KC; ++c) {
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, qf[c % PF]), kreg[c], s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, of[c % PF]),
+                                                     __builtin_bit_cast(bf16x8, vf[c % PF]), dp, 0, 0, 0);
+        if (c + PF < KC) read_step(c + PF);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if ((a.causal && q0 < kw0 + 31) || q0 + BQ > L) {
+        // masked: queries before the key (causal) and past the segment's end
+        int base = q0 + 4 * hi;
+        asm volatile("" : "+v"(base));
+        const int lo = a.causal ? tk_row : 0;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          const int qj = base + 8 * (j >> 2) + (j & 3);
+          if (qj < lo || qj >= L) s[j] = -INFINITY;
+        }
+      }
+      bf16x8 pb[2], dsb[2];
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float p = __builtin_amdgcn_exp2f(s[8 * kk + e] * a.scale_log2);
+          pb[kk][e] = (__bf16)p;
+          dsb[kk][e] = (__bf16)(p * dp[8 * kk + e]);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+      // dV^T += dO^T P and dK^T += Q^T dS, the fragments (queries 16kk + 8t +
+      // 4hi + {0..3}) through transposed reads, one (operand, kk) group ahead.
+      u32x2 tr[2][DB][2];
+      auto read_group = [&](auto G) {
+        constexpr int g = decltype(G)::value, kk = g & 1;
+        const uint32_t base = g < 2 ? oaddr : qaddr;
+        static_for<0, DB>([&](auto DBI) {
+          static_for<0, 2>([&](auto T) {
+            constexpr int db = decltype(DBI)::value, t = decltype(T)::value;
+            tr[g & 1][db][t] = lds_read_tr16<16 * kk * TL::kRowBytes>(base + toff[db][t]);
+          });
+        });
+      };
+      read_group(std::integral_constant<int, 0>{});
+      static_for<0, 4>([&](auto G) {
+        constexpr int g = decltype(G)::value, kk = g & 1;
+        if constexpr (g < 3) {
+          read_group(std::integral_constant<int, g + 1>{});
+          lds_wait<2 * DB>();
+        } else {
+          lds_wait<0>();
+        }
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          lds_bind(tr[kk][db][0]);
+          lds_bind(tr[kk][db][1]);
+          const u32x4 ao = {tr[kk][db][0][0], tr[kk][db][0][1], tr[kk][db][1][0], tr[kk][db][1][1]};
+          if constexpr (g < 2)
+            acc_dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ao), pb[kk], acc_dv[db], 0, 0, 0);
+          else
+            acc_dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ao), dsb[kk], acc_dk[db], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    __syncthreads();
+  }
+
+  // dk = scale * acc_dk and dv = acc_dv, stored scaled per column chunk (the
+  // row maxima are exchanged before any lane leaves).
+  constexpr int CB = kCols<D> / 32;  // accumulators per chunk
+  float mul_k[kChunks<D>], rs_k[kChunks<D>], mul_v[kChunks<D>], rs_v[kChunks<D>];
+#pragma unroll
+  for (int ch = 0; ch < kChunks<D>; ++ch) {
+    float amax_k = 0.0f, amax_v = 0.0f;
+#pragma unroll
+    for (int db = ch * CB; db < (ch + 1) * CB; ++db)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        amax_k = fmaxf(amax_k, fabsf(acc_dk[db][j]));
+        amax_v = fmaxf(amax_v, fabsf(acc_dv[db][j]));
+      }
+    amax_k = fmaxf(amax_k, other_half(amax_k));
+    amax_v = fmaxf(amax_v, other_half(amax_v));
+    row_scale(amax_k * a.scale, a.scale, mul_k[ch], rs_k[ch]);
+    row_scale(amax_v, 1.0f, mul_v[ch], rs_v[ch]);
+  }
+  if (!k_valid) return;
+  const int64_t wrow = (int64_t)it.unit * P.lmax + tk_row;
+  _Float16* krow_out = reinterpret_cast<_Float16*>(a.ws + P.dk_off) + wrow * D;
+  _Float16* vrow_out = reinterpret_cast<_Float16*>(a.ws + P.dv_off) + wrow * D;
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const int d = db * 32 + 8 * jj + 4 * hi;
+      const float mk = mul_k[db / CB], mv = mul_v[db / CB];
+      *reinterpret_cast<f16x4*>(krow_out + d) =
+          f16x4{(_Float16)(acc_dk[db][4 * jj] * mk), (_Float16)(acc_dk[db][4 * jj + 1] * mk),
+                (_Float16)(acc_dk[db][4 * jj + 2] * mk), (_Float16)(acc_dk[db][4 * jj + 3] * mk)};
+      *reinterpret_cast<f16x4*>(vrow_out + d) =
+          f16x4{(_Float16)(acc_dv[db][4 * jj] * mv), (_Float16)(acc_dv[db][4 * jj + 1] * mv),
+                (_Float16)(acc_dv[db][4 * jj + 2] * mv), (_Float16)(acc_dv[db][4 * jj + 3] * mv)};
+    }
+  if (hi == 0)
+#pragma unroll
+    for (int ch = 0; ch < kChunks<D>; ++ch) {
+      reinterpret_cast<float*>(a.ws + P.dk_rec_off)[wrow * kChunks<D> + ch] = rs_k[ch];
+      reinterpret_cast<float*>(a.ws + P.dv_rec_off)[wrow * kChunks<D> + ch] = rs_v[ch];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -699,7 +949,6 @@ hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q
   }
   const dim3 rgrid(static_cast<unsigned>(rblocks));
   const dim3 igrid(static_cast<unsigned>(plan.launch_items));
-  if (2 * plan.launch_items >= (int64_t{1} << 31)) return hipErrorInvalidValue;
   switch (plan.D) {
     case 32:
       hipLaunchKernelGGL(bwd_delta<32>, rgrid, dim3(kThreadsB), 0, stream, da_);
@@ -717,16 +966,14 @@ hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q
       }
       hipLaunchKernelGGL(bwd_sum<64>, rgrid, dim3(kThreadsB), 0, stream, sa);
       break;
-    case 128: {
-      const dim3 igrid2(static_cast<unsigned>(2 * plan.launch_items));
+    case 128:
       hipLaunchKernelGGL(bwd_delta<128>, rgrid, dim3(kThreadsB), 0, stream, da_);
       if (plan.total_items > 0) {
-        hipLaunchKernelGGL(bwd_dq<128>, igrid2, dim3(kThreadsB), 0, stream, a);
-        hipLaunchKernelGGL(bwd_dkdv<128>, igrid2, dim3(kThreadsB), 0, stream, a);
+        hipLaunchKernelGGL(bwd_dq<128>, igrid, dim3(kThreadsB), 0, stream, a);
+        hipLaunchKernelGGL(bwd_dkdv_wide<128>, igrid, dim3(kThreadsB), 0, stream, a);
       }
       hipLaunchKernelGGL(bwd_sum<128>, rgrid, dim3(kThreadsB), 0, stream, sa);
       break;
-    }
     default:
       return hipErrorInvalidValue;
   }

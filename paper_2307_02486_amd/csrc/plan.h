@@ -87,8 +87,7 @@ struct BwdLayout {
   double bytes_combine;  // algorithmic HBM bytes of the delta and sum kernels
 };
 
-// Columns of a compact gradient row that share one scale: the columns one
-// backward work item accumulates.
+// Columns of a compact gradient row that share one scale.
 constexpr int64_t kGradChunk = 64;
 inline int64_t grad_chunks(int64_t D) { return (D + kGradChunk - 1) / kGradChunk; }
 
