@@ -175,8 +175,8 @@ __global__ __launch_bounds__(kThreadsB) void bwd_delta(DeltaArgs a) {
 
 // ---------------------------------------------------------------------------
 // bwd_dq: one work item = 128 query rows of one sparsified segment, all head-dim
-// columns.  Two or three waves per SIMD; the scores start from zero and -lse
-// enters with the scale in one FMA (at D = 128 the 16 registers this frees
+// columns.  Three waves per SIMD, two at D = 128, where the scores start from
+// zero and -lse enters with the scale in one FMA (the 16 registers this frees
 // hold row slices in flight: 250 VGPRs).  D = 128, B = 1, N = 32768, H = 16,
 // patterns (2048, 1), (8192, 2), (32768, 4): 1095 us, against 1877 us when the
 // items ran once per 64-column half (40 instead of 24 MFMAs per block).
@@ -222,11 +222,17 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
   load_rowslices<KC>(static_cast<const u16*>(a.q) + qoff, hi, 1.0f, !q_valid, qreg);
   load_rowslices<KC>(static_cast<const u16*>(a.dout) + qoff, hi, 1.0f, !q_valid, doreg);
   const int64_t srow = ((int64_t)it.b * a.H + it.h) * a.N + it.p0 + (int64_t)qrow * P.r;
-  const float nl = a.nl2[srow] * a.scale_log2;  // -lse in log2 units
-  const float nd = a.nd[srow];
-  f32x16 vnd;
+  // The scores start from -lse/scale where registers allow (D <= 64), and from
+  // zero with -lse added beside the scale otherwise.
+  constexpr bool kLseInit = D <= 64;
+  const float nl2 = a.nl2[srow], nd = a.nd[srow];
+  const float nl = nl2 * a.scale_log2;  // -lse in log2 units
+  f32x16 vs0, vnd;
 #pragma unroll
-  for (int j = 0; j < 16; ++j) vnd[j] = nd;
+  for (int j = 0; j < 16; ++j) {
+    vs0[j] = kLseInit ? nl2 : 0.0f;
+    vnd[j] = nd;
+  }
   f32x16 acc_dq[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) acc_dq[db] = f32x16{};
@@ -268,8 +274,8 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
         };
 #pragma unroll
         for (int c = 0; c < PF; ++c) read_pair(c);
-        __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the MFMAs
-        f32x16 s = f32x16{}, dp = vnd;
+        if constexpr (KC > PF) __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the MFMAs
+        f32x16 s = vs0, dp = vnd;
 #pragma unroll
         for (int c = 0; c < KC; ++c) {
           s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[c % PF]), qreg[c], s, 0, 0, 0);
@@ -285,14 +291,8 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
           for (int j = 0; j < 16; ++j)
             if (base + 8 * (j >> 2) + (j & 3) > 0) s[j] = -INFINITY;
         }
-        // dS^T = P^T (dP - delta)^T as the bf16 B operand of dQ^T += K^T dS^T
-        bf16x8 dsb[2];
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            dsb[kk][e] = (__bf16)(__builtin_amdgcn_exp2f(__builtin_fmaf(s[8 * kk + e], a.scale_log2, nl)) * dp[8 * kk + e]);
-        // K^T fragments through transposed reads (keys kb*32 + 16kk + 8t + 4hi + {0..3})
+        // K^T fragments through transposed reads (keys kb*32 + 16kk + 8t + 4hi +
+        // {0..3}), requested before the softmax (1 % at D = 128)
         u32x2 kt[2][DB][2];
         static_for<0, 2>([&](auto KK) {
           static_for<0, DB>([&](auto DBI) {
@@ -302,6 +302,15 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
             });
           });
         });
+        // dS^T = P^T (dP - delta)^T as the bf16 B operand of dQ^T += K^T dS^T
+        bf16x8 dsb[2];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            dsb[kk][e] = (__bf16)(__builtin_amdgcn_exp2f(kLseInit ? s[8 * kk + e] * a.scale_log2
+                                                             : __builtin_fmaf(s[8 * kk + e], a.scale_log2, nl)) *
+                                dp[8 * kk + e]);
         lds_wait<0>();
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk)
