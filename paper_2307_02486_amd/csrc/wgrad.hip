@@ -4,11 +4,21 @@
 // The reduction is long (tens of thousands of rows) and the output small
 // (E x E), so the work is split along k: workgroup (tile, split) computes a
 // 128 x 128 output tile over one k-chunk into a float32 partial, and a second
-// kernel sums the partials into bf16.  Both operands go from HBM straight to
-// LDS as row-major 64 x 128 tiles (double buffered) and reach the MFMA
-// (v_mfma_f32_32x32x16_bf16) through transposed LDS reads, which give each
-// lane eight consecutive k of one column, the operand layout both A = dY^T
-// and B = X need.  Four waves, each a 64 x 64 quarter of the tile.
+// kernel sums the partials into bf16.  The bias gradient (dY's column sums)
+// comes from the dY tiles already in LDS, as products with a column of ones:
+// dY is not read a second time and no launches are added (K = 32768, M = N =
+// 768 with the bias gradient: 50 us, and 59 us when two more kernels formed it).
+//
+// Both operands go from HBM straight to LDS as row-major 64 x 128 tiles
+// (double buffered) and reach the MFMA (v_mfma_f32_32x32x16_bf16) through
+// transposed LDS reads, which give each lane eight consecutive k of one
+// column, the operand layout both A = dY^T and B = X need.  Four waves, each a
+// 64 x 64 quarter of the tile.  Bound by the tiles' way from L2 into LDS (590
+// MB at the shape above, 14-20 TB/s: with the products taken out the loads
+// alone take 32 of the kernel's 46 us) and the partials.  Measured and not
+// kept: five 32-row stages instead of two of 64 rows (48-50 us for the kernel
+// against 43), eight waves sharing a tile with half the partials (50 us),
+// that with fragments read one step ahead (slower), 256 x 256 tiles (slower).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -28,8 +38,10 @@ struct WgradArgs {
   const u16* dy;
   const u16* x;
   float* part;     // [splits][M][N]
+  float* db_part;  // [splits][db_share][M] column sums of dy
   int64_t K;
   int32_t M, N, chunk, tiles_n, tiles;
+  int32_t db_share;        // column tiles that share out a block row's column sums
   int32_t items, per_xcd;  // tiles * splits, and items per XCD (rounded up)
 };
 
@@ -38,6 +50,7 @@ struct SmemWgrad {
   __attribute__((aligned(16))) u16 b[2][kTileK * kTileMN];
 };
 
+template <bool kBias>
 __global__ __launch_bounds__(kWgThreads) void wgrad_partial(WgradArgs a) {
   __shared__ SmemWgrad sm;
   const int tid = __builtin_amdgcn_workitem_id_x();
@@ -52,7 +65,8 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_partial(WgradArgs a) {
   const int item = (blk & 7) * a.per_xcd + (blk >> 3);
   if (item >= a.items) return;
   const int tile = item % a.tiles, split = item / a.tiles;
-  const int m0 = (tile / a.tiles_n) * kTileMN, n0 = (tile % a.tiles_n) * kTileMN;
+  const int tile_n = tile % a.tiles_n;
+  const int m0 = (tile / a.tiles_n) * kTileMN, n0 = tile_n * kTileMN;
   const int64_t k0 = static_cast<int64_t>(split) * a.chunk;
   const int64_t k1 = k0 + a.chunk < a.K ? k0 + a.chunk : a.K;
   const int ntk = static_cast<int>((k1 - k0 + kTileK - 1) / kTileK);
@@ -105,6 +119,16 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_partial(WgradArgs a) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
 
+  // The column sums of dy are dY^T times a column of ones, formed by one of
+  // the two waves that hold the same rows.  The first db_share tiles of a block
+  // row share its k tiles out: each takes every db_share-th.
+  f32x16 acc_db[2] = {f32x16{}, f32x16{}};
+  bf16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+  const bool has_db = kBias && wn == 0 && tile_n < a.db_share;
+  int db_next = has_db ? tile_n : ntk;
+
   if (ntk > 0) load_tile(0, 0);
   __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
   __syncthreads();
@@ -112,6 +136,7 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_partial(WgradArgs a) {
     const int cur = kt & 1;
     if (kt + 1 < ntk) load_tile(kt + 1, cur ^ 1);
     const uint32_t la = lds_addr(&sm.a[cur][0]), lb = lds_addr(&sm.b[cur][0]);
+    const bool do_db = kt == db_next;
     static_for<0, kTileK / 16>([&](auto KK) {
       constexpr int row = 16 * decltype(KK)::value;  // multiple of 16: the swizzle of rows 0..15
       u32x2 fa[2][2], fb[2][2];
@@ -137,7 +162,12 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_partial(WgradArgs a) {
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[j], acc[i][j], 0, 0, 0);
+      if constexpr (kBias)
+        if (do_db)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) acc_db[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], ones, acc_db[i], 0, 0, 0);
     });
+    if (do_db) db_next += a.db_share;
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();
   }
@@ -156,113 +186,90 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_partial(WgradArgs a) {
           const int n = n0 + wn * 64 + j * 32 + (lane & 31);
           part[static_cast<int64_t>(m) * a.N + n] = acc[i][j][4 * jj + e];
         }
+  if (has_db && (lane & 31) == 0) {
+    // every column of the product with ones is the same: lanes 0 and 32 store theirs
+    float* db = a.db_part + static_cast<int64_t>(split * a.db_share + tile_n) * a.M + m0 + wm * 64 + 4 * hi;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj)
+        *reinterpret_cast<f32x4*>(db + i * 32 + 8 * jj) =
+            f32x4{acc_db[i][4 * jj], acc_db[i][4 * jj + 1], acc_db[i][4 * jj + 2], acc_db[i][4 * jj + 3]};
+  }
 }
 
-__global__ __launch_bounds__(kWgThreads) void wgrad_sum(const float* part, u16* dw, int64_t mn, int splits) {
-  const int64_t i = (static_cast<int64_t>(__builtin_amdgcn_workgroup_id_x()) * kWgThreads +
-                     __builtin_amdgcn_workitem_id_x()) * 4;
-  if (i >= mn) return;
+// dst[i] = the sum over the rows of src [rows][width], rounded to bf16: four
+// columns per thread, the rows over kLanes threads combined through LDS in a
+// fixed order.
+template <int kLanes>
+__device__ inline void sum_rows(const float* src, u16* dst, int64_t width, int rows, int blk, float* red) {
+  constexpr int kCols = kWgThreads / kLanes;
+  const int tid = __builtin_amdgcn_workitem_id_x();
+  const int cl = tid % kCols, rl = tid / kCols;
+  const int64_t i = (static_cast<int64_t>(blk) * kCols + cl) * 4;
   f32x4 s = f32x4{0, 0, 0, 0};
-  for (int p = 0; p < splits; ++p) s += *reinterpret_cast<const f32x4*>(part + p * mn + i);
+  if (i < width)
+#pragma unroll 8
+    for (int p = rl; p < rows; p += kLanes) s += *reinterpret_cast<const f32x4*>(src + p * width + i);
+  if constexpr (kLanes > 1) {
+    if (rl > 0) *reinterpret_cast<f32x4*>(red + 4 * ((rl - 1) * kCols + cl)) = s;
+    __syncthreads();
+    if (rl > 0) return;
+#pragma unroll
+    for (int l = 0; l < kLanes - 1; ++l) s += *reinterpret_cast<const f32x4*>(red + 4 * (l * kCols + cl));
+  }
+  if (i >= width) return;
   u16 o[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) o[e] = __builtin_bit_cast(u16, (__bf16)s[e]);
-  *reinterpret_cast<u32x2*>(dw + i) = u32x2{o[0] | (static_cast<unsigned>(o[1]) << 16),
-                                            o[2] | (static_cast<unsigned>(o[3]) << 16)};
+  *reinterpret_cast<u32x2*>(dst + i) = u32x2{o[0] | (static_cast<unsigned>(o[1]) << 16),
+                                             o[2] | (static_cast<unsigned>(o[3]) << 16)};
 }
 
-// Bias gradient db[m] = sum_k dy[k][m], in two steps.  colsum_partial: the
-// workgroup (column block bx, slice y) sums rows [y rs, (y + 1) rs) of 512
-// columns, each lane 8 columns (one 16-byte load per row) over every fourth
-// row, the four row lanes combined through LDS, into part[y][M].
-__global__ __launch_bounds__(kWgThreads) void colsum_partial(const u16* dy, float* part, int64_t K, int M, int rs,
-                                                             int col_blocks) {
-  __shared__ __attribute__((aligned(16))) float red[4][64 * 8];
-  const int tid = __builtin_amdgcn_workitem_id_x();
-  const int cgl = tid & 63, rl = tid >> 6;
+// dw from the partials; the workgroups from dw_blocks on make db from its rows.
+constexpr int kDbLanes = 8;
+template <int kLanes>
+__global__ __launch_bounds__(kWgThreads) void wgrad_sum(const float* part, u16* dw, int64_t mn, int splits,
+                                                        const float* db_part, u16* db, int M, int R, int dw_blocks) {
+  __shared__ __attribute__((aligned(16))) float red[kWgThreads * 4];
   const int blk = __builtin_amdgcn_workgroup_id_x();
-  const int y = blk / col_blocks;
-  const int cg = (blk % col_blocks) * 64 + cgl;  // group of 8 columns
-  const int64_t r0 = static_cast<int64_t>(y) * rs;
-  const int64_t r1 = r0 + rs < K ? r0 + rs : K;
-  float s[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) s[e] = 0.0f;
-  if (cg < (M >> 3)) {
-#pragma unroll 8
-    for (int64_t r = r0 + rl; r < r1; r += 4) {
-      const u32x4 w = *reinterpret_cast<const u32x4*>(dy + r * M + 8 * cg);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        s[2 * i] += __builtin_bit_cast(float, w[i] << 16);
-        s[2 * i + 1] += __builtin_bit_cast(float, w[i] & 0xffff0000u);
-      }
-    }
-  }
-  *reinterpret_cast<f32x4*>(&red[rl][8 * cgl]) = f32x4{s[0], s[1], s[2], s[3]};
-  *reinterpret_cast<f32x4*>(&red[rl][8 * cgl + 4]) = f32x4{s[4], s[5], s[6], s[7]};
-  __syncthreads();
-  if (rl == 0 && cg < (M >> 3)) {
-    float* out = part + static_cast<int64_t>(y) * M + 8 * cg;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const f32x4 v = (*reinterpret_cast<const f32x4*>(&red[0][8 * cgl + 4 * h]) +
-                       *reinterpret_cast<const f32x4*>(&red[1][8 * cgl + 4 * h])) +
-                      (*reinterpret_cast<const f32x4*>(&red[2][8 * cgl + 4 * h]) +
-                       *reinterpret_cast<const f32x4*>(&red[3][8 * cgl + 4 * h]));
-      *reinterpret_cast<f32x4*>(out + 4 * h) = v;
-    }
-  }
-}
-
-// colsum_final: db[c] = sum over the R slices of part[y][c], 32 columns per
-// workgroup and 8 row lanes per column, combined through LDS; zeros for R = 0.
-__global__ __launch_bounds__(kWgThreads) void colsum_final(const float* part, u16* db, int M, int R) {
-  __shared__ float red[8][32];
-  const int tid = __builtin_amdgcn_workitem_id_x();
-  const int cl = tid & 31, rl = tid >> 5;
-  const int c = __builtin_amdgcn_workgroup_id_x() * 32 + cl;  // M is a multiple of 32
-  float s = 0.0f;
-#pragma unroll 16
-  for (int y = rl; y < R; y += 8) s += part[static_cast<int64_t>(y) * M + c];
-  red[rl][cl] = s;
-  __syncthreads();
-  if (rl == 0) {
-    const float t = ((red[0][cl] + red[1][cl]) + (red[2][cl] + red[3][cl])) +
-                    ((red[4][cl] + red[5][cl]) + (red[6][cl] + red[7][cl]));
-    db[c] = __builtin_bit_cast(u16, (__bf16)t);
-  }
+  if (blk < dw_blocks) sum_rows<kLanes>(part, dw, mn, splits, blk, red);
+  else sum_rows<kDbLanes>(db_part, db, M, R, blk - dw_blocks, red);
 }
 
 }  // namespace
 
-// Slices of the bias-gradient column sums: 256 rows each, at most 1024.
-int64_t colsum_slices(int64_t K, int64_t* rows_per_slice) {
-  *rows_per_slice = 0;
+// Rows of M floats kept for the column sums: one per 256 rows of dy, at most 1024.
+static int64_t db_rows(int64_t K) {
   if (K <= 0) return 0;
-  int64_t R = (K + 255) / 256;
-  if (R > 1024) R = 1024;
-  *rows_per_slice = (K + R - 1) / R;
-  return (K + *rows_per_slice - 1) / *rows_per_slice;
-}
-
-uint64_t wgrad_workspace(int64_t K, int64_t M, int64_t N) {
-  int64_t chunk = 0, rs = 0;
-  return (static_cast<uint64_t>(wgrad_splits(K, M, N, &chunk)) * N + colsum_slices(K, &rs)) * M * 4;
+  const int64_t R = std::min<int64_t>(1024, (K + 255) / 256);
+  const int64_t rows = (K + R - 1) / R;
+  return (K + rows - 1) / rows;
 }
 
 // Splits of the reduction: at most 512 workgroups in all (two per compute
 // unit, as 64 KiB of LDS per workgroup allows) unless the output alone has
-// more tiles, each split a whole number of k tiles; no split for K = 0 (dW
-// is then zero).
-int64_t wgrad_splits(int64_t K, int64_t M, int64_t N, int64_t* chunk) {
+// more tiles, each split a whole number of k tiles and `least` rows if there
+// are that many; no split for K = 0 (dW is then zero).
+static int64_t splits_of(int64_t K, int64_t M, int64_t N, int64_t least, int64_t* chunk) {
   *chunk = 0;
   if (K <= 0) return 0;
   const int64_t tiles = (M / kTileMN) * (N / kTileMN);
   const int64_t ktiles = (K + kTileK - 1) / kTileK;
-  const int64_t s = std::max<int64_t>(1, std::min<int64_t>(512 / tiles, ktiles));
+  const int64_t s = std::max<int64_t>(1, std::min<int64_t>(512 / tiles, ktiles * kTileK / least));
   *chunk = (ktiles + s - 1) / s * kTileK;
   return (K + *chunk - 1) / *chunk;
+}
+
+// 256 rows per split at least: a split costs a partial output, written and
+// read, and for small outputs the sum over many of them is a long chain (K =
+// 32768, M = N = 128: 144 us for a call with its 512 splits of 64 rows, 17 us with 128).
+int64_t wgrad_splits(int64_t K, int64_t M, int64_t N, int64_t* chunk) { return splits_of(K, M, N, 256, chunk); }
+
+// Room for splits of a single k tile, of which wgrad_splits never has more.
+uint64_t wgrad_workspace(int64_t K, int64_t M, int64_t N) {
+  int64_t chunk = 0;
+  return static_cast<uint64_t>(splits_of(K, M, N, kTileK, &chunk) * N + db_rows(K)) * M * 4;
 }
 
 hipError_t launch_wgrad(const void* dy, const void* x, void* dw, void* db, int64_t K, int64_t M, int64_t N,
@@ -281,23 +288,26 @@ hipError_t launch_wgrad(const void* dy, const void* x, void* dw, void* db, int64
   a.tiles = static_cast<int32_t>((M / kTileMN) * (N / kTileMN));
   a.items = static_cast<int32_t>(a.tiles * splits);
   a.per_xcd = (a.items + 7) / 8;
-  if (splits > 0)
-    hipLaunchKernelGGL(wgrad_partial, dim3(static_cast<unsigned>(8 * a.per_xcd)), dim3(kWgThreads), 0, stream, a);
-  const int64_t mn = M * N;
-  hipLaunchKernelGGL(wgrad_sum, dim3(static_cast<unsigned>((mn / 4 + kWgThreads - 1) / kWgThreads)),
-                     dim3(kWgThreads), 0, stream, static_cast<const float*>(workspace), static_cast<u16*>(dw), mn,
-                     static_cast<int>(splits));
-  if (db) {
-    int64_t rs = 0;
-    const int64_t R = colsum_slices(K, &rs);
-    float* part = static_cast<float*>(workspace) + splits * mn;
-    const int col_blocks = static_cast<int>((M / 8 + 63) / 64);
-    if (R > 0)
-      hipLaunchKernelGGL(colsum_partial, dim3(static_cast<unsigned>(R * col_blocks)), dim3(kWgThreads), 0, stream,
-                         static_cast<const u16*>(dy), part, K, static_cast<int>(M), static_cast<int>(rs), col_blocks);
-    hipLaunchKernelGGL(colsum_final, dim3(static_cast<unsigned>(M / 32)), dim3(kWgThreads), 0, stream,
-                       static_cast<const float*>(part), static_cast<u16*>(db), static_cast<int>(M), static_cast<int>(R));
+  // every split has a row of its own for the column sums at least (the splits
+  // are at most K / 256, or one)
+  a.db_part = a.part + splits * M * N;
+  a.db_share = splits > 0 ? static_cast<int32_t>(std::min<int64_t>(a.tiles_n, db_rows(K) / splits)) : 0;
+  const dim3 grid(static_cast<unsigned>(8 * a.per_xcd));
+  if (splits > 0) {
+    if (db) hipLaunchKernelGGL(wgrad_partial<true>, grid, dim3(kWgThreads), 0, stream, a);
+    else hipLaunchKernelGGL(wgrad_partial<false>, grid, dim3(kWgThreads), 0, stream, a);
   }
+  // K = 0: no partials, the sums below write zeros
+  const int64_t mn = M * N;
+  // One thread sums all splits of its columns where that makes 256 workgroups
+  // (768 x 768, 14 splits: 6.3 us, 8.3 with four), four threads below that.
+  const int lanes = mn >= 256 * 4 * kWgThreads ? 1 : 4;
+  const int dw_blocks = static_cast<int>((mn * lanes + 4 * kWgThreads - 1) / (4 * kWgThreads));
+  const int db_blocks = db ? static_cast<int>((M * kDbLanes + 4 * kWgThreads - 1) / (4 * kWgThreads)) : 0;
+  hipLaunchKernelGGL(lanes == 1 ? wgrad_sum<1> : wgrad_sum<4>, dim3(static_cast<unsigned>(dw_blocks + db_blocks)),
+                     dim3(kWgThreads), 0, stream, static_cast<const float*>(a.part), static_cast<u16*>(dw), mn,
+                     static_cast<int>(splits), static_cast<const float*>(a.db_part), static_cast<u16*>(db),
+                     static_cast<int>(M), static_cast<int>(splits * a.db_share), dw_blocks);
   return hipGetLastError();
 }
 

@@ -99,3 +99,26 @@ def test_wgrad_errors_launch_nothing():
     assert e.value.name == "DA_EUNSUPPORTED"
     torch.cuda.synchronize()
     assert (out == 5).all().item()
+
+
+@pytest.mark.parametrize("case", [
+    (255, 128, 1024),      # one row for the column sums: one column tile forms them all
+    (513, 256, 384),       # fewer rows than column tiles, two splits' worth of k tiles
+    (32768, 128, 128),     # many splits of a small output, four threads per column sum
+    (2560, 2048, 256),     # the output just large enough for one thread per column
+    (64, 128, 2048),       # one k tile, more column tiles than k tiles
+], ids=str)
+def test_wgrad_bias_from_shared_tiles(case):
+    """dw and db where the column sums are shared out differently, with the
+    bars of the module docstring."""
+    from paper_2307_02486_amd import wgrad
+    K, M, N = case
+    note(f"[wgrad] shared K={K} M={M} N={N}")
+    dy = workloads.make_random((K, M), torch.bfloat16, 1.0, 910 + M, "cuda", 0)
+    x = workloads.make_random((K, N), torch.bfloat16, 1.0, 911 + N, "cuda", 0)
+    dw, db = wgrad(dy, x, bias_grad=True)
+    torch.cuda.synchronize()
+    _check(dw, dy, x)
+    ref = dy.float().sum(0)
+    bound = 2.0 ** -8 * ref.abs() + 2.0 ** -12 * dy.float().abs().sum(0)
+    assert float(((db.float() - ref).abs() / bound).max()) <= 1.0
