@@ -48,6 +48,41 @@ def _pattern_array_cached(pats: tuple):
     return _lib.pattern_array(pats)
 
 
+@functools.lru_cache(maxsize=256)
+def _prepared_cached(entry: str, B: int, N: int, H: int, D: int, patterns: tuple, causal: int, dtype_code: int,
+                     scale: float):
+    pats = _pattern_key(patterns)
+    info = _plan_cached(entry, B, N, H, D, pats, causal, dtype_code, scale)
+    return (max(256, int(info["workspace_bytes"])), *_pattern_array_cached(pats))
+
+
+def _prepared(entry: str, shape, patterns, causal: int, dtype_code: int, scale: float):
+    """(workspace bytes, ctypes pattern array, pattern count) of a call: one
+    look-up by the patterns as given, if they can be a key."""
+    patterns = tuple(patterns)
+    try:
+        return _prepared_cached(entry, *shape, patterns, causal, dtype_code, scale)
+    except TypeError:  # patterns given as lists
+        return _prepared_cached(entry, *shape, _pattern_key(patterns), causal, dtype_code, scale)
+
+
+@functools.lru_cache(maxsize=256)
+def _workspace_bytes(entry: str, *dims: int) -> int:
+    """The workspace size a dilated_attn_*_workspace entry point reports."""
+    lib = _lib.load()
+    need = ctypes.c_uint64(0)
+    rc = getattr(lib, entry)(*dims, ctypes.byref(need))
+    if rc != 0:
+        raise _lib.DilatedAttnError(rc, lib)
+    return need.value
+
+
+def _raw_stream(device: torch.device) -> int:
+    """The HIP stream of torch's current stream on a device (the stream object
+    that torch.cuda.current_stream builds costs 2 us a call)."""
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
 def plan(B: int, N: int, H: int, D: int, patterns: Sequence[Tuple[int, int]], causal: bool = True,
          dtype=torch.bfloat16, scale: float | None = None) -> dict:
     """Validate a problem and return its workspace size and work counts (host only)."""
@@ -80,8 +115,8 @@ def _check_like(name: str, t: torch.Tensor, shape, dtype, device):
 def _stream_use(stream, owned):
     """Tensors this binding allocated on torch's current stream but handed to
     another stream's kernels: tell the allocator, so that their memory is not
-    reused before that stream's work is done."""
-    if stream != torch.cuda.current_stream(stream.device):
+    reused before that stream's work is done.  stream None: the current one."""
+    if stream is not None and stream != torch.cuda.current_stream(stream.device):
         for t in owned:
             t.record_stream(stream)
 
@@ -107,10 +142,9 @@ def dilated_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
         if not t.is_contiguous() or t.shape != q.shape or t.dtype != q.dtype or t.device != q.device:
             raise ValueError("q, k, v must be contiguous tensors of the same shape, dtype and device")
     B, N, H, D = q.shape
-    pats = _pattern_key(patterns)
     dcode = _dtype_code(q.dtype)
     sc = float(scale or 0.0)
-    info = _plan_cached("dilated_attn_plan", B, N, H, D, pats, int(bool(causal)), dcode, sc)
+    ws_bytes, arr, n = _prepared("dilated_attn_plan", q.shape, patterns, int(bool(causal)), dcode, sc)
     owned = []
     if out is None:
         out = torch.empty_like(q)
@@ -123,16 +157,14 @@ def dilated_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
     else:
         _check_like("lse", lse, (B, H, N), torch.float32, q.device)
     if workspace is None:
-        workspace = torch.empty(max(256, int(info["workspace_bytes"])), dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=q.device)
         owned.append(workspace)
     elif workspace.dtype != torch.uint8 or workspace.device != q.device or not workspace.is_contiguous():
         raise ValueError("workspace must be a contiguous uint8 tensor on q's device")
-    if stream is None:
-        stream = torch.cuda.current_stream(q.device)
-    arr, n = _pattern_array_cached(pats)
+    raw = _raw_stream(q.device) if stream is None else stream.cuda_stream
     rc = lib.dilated_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
                               B, N, H, D, arr, n, int(bool(causal)), dcode, sc,
-                              workspace.data_ptr(), workspace.numel(), stream.cuda_stream)
+                              workspace.data_ptr(), workspace.numel(), raw)
     if rc != 0:
         raise _lib.DilatedAttnError(rc, lib)
     _stream_use(stream, owned)
@@ -201,10 +233,9 @@ def dilated_attn_bwd(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, out: tor
             raise ValueError("q, k, v, out, dout must be contiguous tensors of the same shape, dtype, device")
     B, N, H, D = q.shape
     _check_like("lse", lse, (B, H, N), torch.float32, q.device)
-    pats = _pattern_key(patterns)
     dcode = _dtype_code(q.dtype)
     sc = float(scale or 0.0)
-    info = _plan_cached("dilated_attn_bwd_plan", B, N, H, D, pats, int(bool(causal)), dcode, sc)
+    ws_bytes, arr, n = _prepared("dilated_attn_bwd_plan", q.shape, patterns, int(bool(causal)), dcode, sc)
     owned = []
     grads = []
     for name, g in (("dq", dq), ("dk", dk), ("dv", dv)):
@@ -216,17 +247,15 @@ def dilated_attn_bwd(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, out: tor
         grads.append(g)
     dq, dk, dv = grads
     if workspace is None:
-        workspace = torch.empty(max(256, int(info["workspace_bytes"])), dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=q.device)
         owned.append(workspace)
     elif workspace.dtype != torch.uint8 or workspace.device != q.device or not workspace.is_contiguous():
         raise ValueError("workspace must be a contiguous uint8 tensor on q's device")
-    if stream is None:
-        stream = torch.cuda.current_stream(q.device)
-    arr, n = _pattern_array_cached(pats)
+    raw = _raw_stream(q.device) if stream is None else stream.cuda_stream
     rc = lib.dilated_attn_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
                               dout.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), B, N, H, D,
                               arr, n, int(bool(causal)), dcode, sc,
-                              workspace.data_ptr(), workspace.numel(), stream.cuda_stream)
+                              workspace.data_ptr(), workspace.numel(), raw)
     if rc != 0:
         raise _lib.DilatedAttnError(rc, lib)
     _stream_use(stream, owned)
@@ -248,11 +277,10 @@ def xpos(x: torch.Tensor, sign: int, transpose: bool = False, center: int | None
     out = torch.empty_like(x) if out is None else out
     if out.shape != x.shape or out.dtype != x.dtype or out.device != x.device or not out.is_contiguous():
         raise ValueError("out must be a contiguous tensor like x")
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device)
+    raw = _raw_stream(x.device) if stream is None else stream.cuda_stream
     rc = lib.dilated_attn_xpos(x.data_ptr(), out.data_ptr(), B, N, H, D, int(sign), int(bool(transpose)),
                                N // 2 if center is None else int(center), float(base), float(gamma),
-                               float(scale_base), _dtype_code(x.dtype), stream.cuda_stream)
+                               float(scale_base), _dtype_code(x.dtype), raw)
     if rc != 0:
         raise _lib.DilatedAttnError(rc, lib)
     return out
@@ -272,22 +300,18 @@ def wgrad(dy: torch.Tensor, x: torch.Tensor, out: torch.Tensor | None = None, bi
         raise ValueError("dy [K, M] and x [K, N] must be contiguous 2-D tensors of one dtype")
     K, M = dy.shape
     N = x.shape[1]
-    need = ctypes.c_uint64(0)
-    rc = lib.dilated_attn_wgrad_workspace(K, M, N, ctypes.byref(need))
-    if rc != 0:
-        raise _lib.DilatedAttnError(rc, lib)
+    need = _workspace_bytes("dilated_attn_wgrad_workspace", K, M, N)
     out = torch.empty((M, N), dtype=dy.dtype, device=dy.device) if out is None else out
     if out.shape != (M, N) or out.dtype != dy.dtype or out.device != dy.device or not out.is_contiguous():
         raise ValueError("out must be a contiguous [M, N] tensor of dy's dtype")
-    ws = torch.empty(max(need.value, 16), dtype=torch.uint8, device=dy.device)
-    if stream is None:
-        stream = torch.cuda.current_stream(dy.device)
+    ws = torch.empty(max(need, 16), dtype=torch.uint8, device=dy.device)
+    raw = _raw_stream(dy.device) if stream is None else stream.cuda_stream
     db = torch.empty((M,), dtype=dy.dtype, device=dy.device) if bias_grad else None
     rc = lib.dilated_attn_wgrad(dy.data_ptr(), x.data_ptr(), out.data_ptr(), db.data_ptr() if bias_grad else None,
-                                K, M, N, _dtype_code(dy.dtype), ws.data_ptr(), need.value, stream.cuda_stream)
+                                K, M, N, _dtype_code(dy.dtype), ws.data_ptr(), need, raw)
     if rc != 0:
         raise _lib.DilatedAttnError(rc, lib)
-    ws.record_stream(stream)
+    _stream_use(stream, [ws])
     return (out, db) if bias_grad else out
 
 
@@ -311,11 +335,10 @@ def layer_norm(x: torch.Tensor, weight: torch.Tensor, bias: torch.Tensor, eps: f
     y = torch.empty_like(x)
     mean = torch.empty(x.shape[:-1], dtype=torch.float32, device=x.device)
     rstd = torch.empty_like(mean)
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device)
+    raw = _raw_stream(x.device) if stream is None else stream.cuda_stream
     rc = lib.dilated_attn_layernorm_fwd(x.data_ptr(), weight.data_ptr(), bias.data_ptr(), y.data_ptr(),
                                         mean.data_ptr(), rstd.data_ptr(), rows, E, float(eps),
-                                        _dtype_code(x.dtype), stream.cuda_stream)
+                                        _dtype_code(x.dtype), raw)
     if rc != 0:
         raise _lib.DilatedAttnError(rc, lib)
     return y, mean, rstd
@@ -339,20 +362,16 @@ def layer_norm_bwd(dy: torch.Tensor, x: torch.Tensor, weight: torch.Tensor, mean
     if mean.numel() != rows or rstd.numel() != rows or mean.dtype != torch.float32 or rstd.dtype != torch.float32 \
             or not mean.is_contiguous() or not rstd.is_contiguous() or not weight.is_contiguous():
         raise ValueError("mean and rstd must be contiguous float32 tensors of one value per row")
-    need = ctypes.c_uint64(0)
-    rc = lib.dilated_attn_layernorm_bwd_workspace(rows, E, ctypes.byref(need))
-    if rc != 0:
-        raise _lib.DilatedAttnError(rc, lib)
+    need = _workspace_bytes("dilated_attn_layernorm_bwd_workspace", rows, E)
     dx = torch.empty_like(x)
     dw = torch.empty((E,), dtype=x.dtype, device=x.device)
     db = torch.empty_like(dw)
-    ws = torch.empty(max(need.value, 16), dtype=torch.uint8, device=x.device)
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device)
+    ws = torch.empty(max(need, 16), dtype=torch.uint8, device=x.device)
+    raw = _raw_stream(x.device) if stream is None else stream.cuda_stream
     rc = lib.dilated_attn_layernorm_bwd(dy.data_ptr(), x.data_ptr(), weight.data_ptr(), mean.data_ptr(),
                                         rstd.data_ptr(), dx.data_ptr(), dw.data_ptr(), db.data_ptr(), rows, E,
-                                        _dtype_code(x.dtype), ws.data_ptr(), need.value, stream.cuda_stream)
+                                        _dtype_code(x.dtype), ws.data_ptr(), need, raw)
     if rc != 0:
         raise _lib.DilatedAttnError(rc, lib)
-    ws.record_stream(stream)
+    _stream_use(stream, [ws])
     return dx, dw, db
