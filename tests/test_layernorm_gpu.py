@@ -118,3 +118,18 @@ def test_layernorm_errors_launch_nothing():
     with pytest.raises(DilatedAttnError) as e:
         layer_norm(x, w, w)
     assert e.value.name == "DA_EUNSUPPORTED"
+
+
+@pytest.mark.parametrize("case", [
+    # rows at which a wave takes one, two and five rows; widths of one to eight
+    # 256-element parts with the last part ragged
+    (3072, 264, 1.0, 0.0),
+    (3073, 520, 1.0, 0.0),
+    (12289, 248, 1.0, 0.0),
+    (3100, 1288, 1.0, 0.0),
+    (100, 1536, 1.0, 0.0),
+    (70, 1800, 1.0, 5.0),
+    (5, 1024, 1.0, 0.0),
+], ids=str)
+def test_layernorm_row_and_width_variants(case):
+    test_layernorm_matches_float32(case)
