@@ -42,7 +42,7 @@ struct AttnArgs {
 // bf16 MFMA kernel
 // ---------------------------------------------------------------------------
 constexpr int kThreads = 256;  // four waves of 32 query rows each
-constexpr int kBM = 128;       // query rows per work item
+constexpr int kBM = 128;       // query rows per work item (64 with split keys)
 #ifndef DA_KEY_TILE
 #define DA_KEY_TILE 64
 #endif
@@ -69,13 +69,19 @@ struct SmemBf16 {
   int redo;  // set by a wave whose tile sums left the fast path's range
 };
 
-template <int D, bool kBufferLoads>
+// KS = 1: each of the four waves holds 32 query rows and takes every key.
+// KS = 2 (small launches, see launch_attention): two blocks of 32 query rows
+// times two halves of the keys; the wave of half w takes the 32-key block w of
+// every 64-key tile, and the halves' (max, sum, O) meet in LDS at the end.
+template <int D, bool kBufferLoads, int KS>
 __global__ __launch_bounds__(kThreads) void attn_fwd_bf16(AttnArgs a) {
   static_assert(D % 32 == 0, "head dim must be a multiple of 32");
+  static_assert(kBN == 64, "two 32-key blocks per tile");
   constexpr int BN = kBN;
+  constexpr int BM = kBM / KS;
   constexpr int KC = D / 16;  // MFMA k-steps over the head dim
   constexpr int DB = D / 32;  // 32-wide blocks of the head dim in O^T
-  constexpr int SB = BN / 32; // 32-key blocks of S^T per tile
+  constexpr int SB = BN / 32 / KS;  // 32-key blocks of S^T per wave and tile
   using TL = TileLayout<D>;
   // A wave's load instruction fills 64 consecutive 16-byte LDS slots.
   constexpr int kLoadsPerWave = BN * TL::kSlots / 64 / (kThreads / 64);
@@ -83,7 +89,7 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_bf16(AttnArgs a) {
   __shared__ SmemBf16<D> sm;
 
   Item it;
-  if (!decode_item(a, __builtin_amdgcn_workgroup_id_x(), kBM, it)) return;
+  if (!decode_item(a, __builtin_amdgcn_workgroup_id_x(), BM, it)) return;
   const PatArgs& P = a.pat[it.pi];
   const u16* __restrict__ qg = static_cast<const u16*>(a.q);
 
@@ -93,9 +99,11 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_bf16(AttnArgs a) {
   const int qr = lane & 31;   // query column of this lane in S^T / O^T
   const int hi = lane >> 5;   // half-wave
   const int L = it.L;
-  const int q0 = it.tq * kBM;
-  const int qend = min(q0 + kBM, L);
-  const int tq_row = q0 + wv * 32 + qr;  // this lane's query (kept-row index)
+  const int qb = KS == 1 ? wv : wv & 1;           // this wave's query block
+  const int kh = KS == 1 ? 0 : wv >> 1;           // and key half
+  const int q0 = it.tq * BM;
+  const int qend = min(q0 + BM, L);
+  const int tq_row = q0 + qb * 32 + qr;  // this lane's query (kept-row index)
   const bool q_valid = tq_row < L;
   const int64_t row_step = it.rstride * D;  // elements between consecutive kept rows
   const float c = a.scale_log2;             // > 0
@@ -164,7 +172,7 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_bf16(AttnArgs a) {
 
   const int kv_end = a.causal ? qend : L;
   const int ntile = (kv_end + BN - 1) / BN;
-  const int wq_lo = q0 + wv * 32;  // smallest query of this wave
+  const int wq_lo = q0 + qb * 32;  // smallest query of this wave
   const int lim = a.causal ? min(tq_row, L - 1) : L - 1;  // last visible key of this lane
   // Lane roles in the transposed V reads (ds_read_b64_tr_b16): within each
   // 16-lane group, lane 4r + cb supplies the address of key row r, head-dim
@@ -203,14 +211,15 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_bf16(AttnArgs a) {
   __syncthreads();
   for (int jt = 0; jt < ntile; ++jt) {
     const int cur = jt & 1;
-    const int k0 = jt * BN;
+    const int k0 = jt * BN + kh * 32;  // first key of this wave's share of the tile
     const bool more = jt + 1 < ntile;
     if (more) load_tile(jt + 1, cur ^ 1);
-    const char* kl = reinterpret_cast<const char*>(&sm.k[cur][0]);
-    const char* vl = reinterpret_cast<const char*>(&sm.v[cur][0]);
+    const char* kl = reinterpret_cast<const char*>(&sm.k[cur][0]) + kh * 32 * TL::kRowBytes;
+    const char* vl = reinterpret_cast<const char*>(&sm.v[cur][0]) + kh * 32 * TL::kRowBytes;
 
-    // Tiles entirely after this wave's queries are skipped (causal).
-    if (!(a.causal && k0 > wq_lo + 31)) {
+    // Keys entirely after this wave's queries are skipped (causal), and a
+    // half's blocks past the segment.
+    if (!(a.causal && k0 > wq_lo + 31) && (KS == 1 || k0 < L)) {
       // S^T = K Q^T (unscaled fp32 scores), one 32x32 block per 32 keys; the
       // K fragments of a group of QG blocks are requested from LDS before the
       // group's MFMAs.
@@ -235,7 +244,7 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_bf16(AttnArgs a) {
         }
       }
       // Mask keys after the query (causal) and past the segment's end.
-      if ((a.causal && k0 + BN - 1 > wq_lo) || k0 + BN > L) {
+      if ((a.causal && k0 + 32 * SB - 1 > wq_lo) || k0 + 32 * SB > L) {
         int base = k0 + 4 * hi - lim;   // key - lim = base + offset(kb, j)
         // Opaque to the compiler, so that the compares are made here: hoisted
         // out of the loops (for the first tile) they become 32 lane masks held
@@ -348,6 +357,37 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_bf16(AttnArgs a) {
   load_tile(0, 0);
   }
 
+  if constexpr (KS == 2) {
+    // The second half's results join the first's through LDS (the tiles are no
+    // longer read: the loop ended with a barrier).  A half that saw no key has
+    // sum and O zero and the smallest max.
+    constexpr int kStg = (16 * DB + 2) * 64;
+    float* stg = reinterpret_cast<float*>(&sm.k[0][0]) + qb * kStg + lane;
+    static_assert(2 * kStg * sizeof(float) <= sizeof(sm.k) + sizeof(sm.v), "fits the tiles");
+    if (kh == 1) {
+      stg[0] = (a.causal && 32 > wq_lo + 31) || 32 >= L ? kNegBig : m_run;
+      stg[64] = l_run;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) stg[(2 + 16 * db + j) * 64] = acc_o[db][j];
+    }
+    __syncthreads();
+    if (kh == 0) {
+      const float m1 = stg[0];
+      const float m_tot = fmaxf(m_run, m1);
+      const float w0 = __builtin_amdgcn_exp2f(m_run - m_tot), w1 = __builtin_amdgcn_exp2f(m1 - m_tot);
+      m_run = m_tot;
+      l_run = l_run * w0 + stg[64] * w1;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc_o[db][j] = acc_o[db][j] * w0 + stg[(2 + 16 * db + j) * 64] * w1;
+    }
+    __syncthreads();  // read before the rows are staged over it
+    if (kh == 1) return;
+  }
+
   // Epilogue: normalise this wave's 32 rows of the per-pattern output, scale
   // each row by its power of two and stage the fp16 rows in a private LDS
   // region (the tiles are no longer read: the loop ended with a barrier), so
@@ -365,7 +405,7 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_bf16(AttnArgs a) {
   amax = fmaxf(amax, other_half(amax));
   float mul, rscale;
   row_scale(amax * inv, inv, mul, rscale);
-  char* stg = reinterpret_cast<char*>(&sm.k[0][0]) + wv * 32 * TL::kRowBytes;
+  char* stg = reinterpret_cast<char*>(&sm.k[0][0]) + qb * 32 * TL::kRowBytes;
   auto stg_off = [&](int row, int chunk) {
     return row * TL::kRowBytes + ((chunk ^ ((row >> 1) & (TL::kSlots - 1))) << 4);
   };
@@ -625,6 +665,19 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_f32(AttnArgs a) {
     reinterpret_cast<f32x2*>(a.ws + P.lse_off)[wrow] = f32x2{(m_tot + __builtin_amdgcn_logf(l_tot)) * kLn2, 1.0f};
 }
 
+template <int D>
+void launch_bf16(bool offsets32, bool split, const dim3& grid, hipStream_t stream, const AttnArgs& a) {
+  if (split) {
+    if (offsets32) hipLaunchKernelGGL((attn_fwd_bf16<D, true, 2>), grid, dim3(kThreads), 0, stream, a);
+    else hipLaunchKernelGGL((attn_fwd_bf16<D, false, 2>), grid, dim3(kThreads), 0, stream, a);
+  } else {
+    if (offsets32) hipLaunchKernelGGL((attn_fwd_bf16<D, true, 1>), grid, dim3(kThreads), 0, stream, a);
+    else hipLaunchKernelGGL((attn_fwd_bf16<D, false, 1>), grid, dim3(kThreads), 0, stream, a);
+  }
+}
+
+constexpr int64_t kSplitItems = 512;  // see the rule in launch_attention
+
 }  // namespace
 
 hipError_t launch_attention(const Plan& plan, const void* q, const void* k, const void* v,
@@ -639,28 +692,39 @@ hipError_t launch_attention(const Plan& plan, const void* q, const void* k, cons
   a.H = static_cast<int32_t>(plan.H);
   a.causal = plan.causal;
   a.scale_log2 = plan.scale * kLog2e;
+  // A launch of at most 512 items of 128 rows (two per CU) leaves the chip
+  // waiting for the longest items' chains: 64-row items with split keys halve
+  // those.  Attention launch, us, 128-row items -> split: 12 heads of 64, the
+  // paper's five patterns: N = 1024 (204 items) 18.9 -> 15.9, 2048 (396) 30.6
+  // -> 28.4, 3072 (672) 33.2 -> 33.1, 4096 (780) 40.6 -> 43.2; causal dense, 8
+  // heads, N = 8192 (512) 106 -> 92; D = 128, 8 heads, N = 2048 (264) 44 -> 34;
+  // D = 32, B = 2, N = 5003, three patterns (720) 19.3 -> 21.5.
+  const bool split = plan.dtype == DA_BF16 && plan.total_items <= kSplitItems;
+  const int64_t bm = split ? kBM / 2 : plan.block_m;
+  auto tiles = [&](const PatternPlan& pp) { return (pp.lmax + bm - 1) / bm; };
   // The patterns of the launch, most query tiles per unit first.
   int order[DA_MAX_PATTERNS];
   const int n = plan.npat;
   for (int i = 0; i < n; ++i) order[i] = i;
-  std::stable_sort(order, order + n, [&](int x, int y) { return plan.pat[x].ntiles > plan.pat[y].ntiles; });
+  std::stable_sort(order, order + n, [&](int x, int y) { return tiles(plan.pat[x]) > tiles(plan.pat[y]); });
   a.npat = n;
   int64_t items = 0, launch = 0;
   for (int i = 0; i < DA_MAX_PATTERNS; ++i) {
     PatArgs& pa = a.pat[i];
     if (i < n) {
       const PatternPlan& pp = plan.pat[order[i]];
+      const int64_t nt = tiles(pp);
       pa.w = static_cast<int32_t>(pp.w);
       pa.r = static_cast<int32_t>(pp.r);
       pa.nseg = static_cast<int32_t>(pp.nseg);
       pa.lmax = static_cast<int32_t>(pp.lmax);
-      pa.ntiles = static_cast<int32_t>(pp.ntiles);
+      pa.ntiles = static_cast<int32_t>(nt);
       pa.units = static_cast<int32_t>(pp.units);
       pa.o_off = static_cast<int64_t>(pp.o_off);
       pa.lse_off = static_cast<int64_t>(pp.lse_off);
-      items += pp.units * pp.ntiles;
+      items += pp.units * nt;
       // XCD 0 holds the most units of every pattern; the launch covers 8 times its slots.
-      launch += (pp.units + 7) / 8 * pp.ntiles * 8;
+      launch += (pp.units + 7) / 8 * nt * 8;
     } else {
       pa = PatArgs{1, 1, 1, 1, 1, 0, 0, 0};
     }
@@ -671,16 +735,13 @@ hipError_t launch_attention(const Plan& plan, const void* q, const void* k, cons
   if (plan.dtype == DA_BF16) {
     switch (plan.D) {
       case 32:
-        if (plan.offsets32) hipLaunchKernelGGL((attn_fwd_bf16<32, true>), grid, dim3(kThreads), 0, stream, a);
-        else hipLaunchKernelGGL((attn_fwd_bf16<32, false>), grid, dim3(kThreads), 0, stream, a);
+        launch_bf16<32>(plan.offsets32, split, grid, stream, a);
         break;
       case 64:
-        if (plan.offsets32) hipLaunchKernelGGL((attn_fwd_bf16<64, true>), grid, dim3(kThreads), 0, stream, a);
-        else hipLaunchKernelGGL((attn_fwd_bf16<64, false>), grid, dim3(kThreads), 0, stream, a);
+        launch_bf16<64>(plan.offsets32, split, grid, stream, a);
         break;
       case 128:
-        if (plan.offsets32) hipLaunchKernelGGL((attn_fwd_bf16<128, true>), grid, dim3(kThreads), 0, stream, a);
-        else hipLaunchKernelGGL((attn_fwd_bf16<128, false>), grid, dim3(kThreads), 0, stream, a);
+        launch_bf16<128>(plan.offsets32, split, grid, stream, a);
         break;
       default: return hipErrorInvalidValue;
     }

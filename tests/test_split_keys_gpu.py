@@ -1,0 +1,52 @@
+"""The bf16 forward's two forms: 64-row items whose keys are split over two
+waves (launches of at most 512 items of 128 rows) and 128-row items, each
+against the oracle where it can go wrong.  Bars: those of the bf16 parity tests
+(2e-2 on out, 1e-2 on lse: bf16 probabilities and outputs of size about 1)."""
+import pytest
+import torch
+
+import workloads
+from tests.gpu_util import compare_full, note, require_gpu
+from tests.test_parity_gpu import LOG2E, REGIME_SCALES, _integer_qkv
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    require_gpu()
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 65, 96, 97, 129, 193])
+def test_split_tile_edges(n, D, causal):
+    """Rows and keys at the edges of 32-query blocks, 32-key halves and 64-key
+    tiles: halves that see no key, segments that end inside either half."""
+    note(f"[split] N={n} D={D} causal={causal}")
+    q, k, v = (workloads.make_random((1, n, 3, D), torch.bfloat16, 1.0, 300 + n, "cuda", t) for t in range(3))
+    compare_full(q, k, v, [(n, 1), (max(2, n // 2 + 1), 2)], causal, "bf16", tag=f"N{n} D{D}")
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("regime,jump", [("rescale", 2.0), ("rerun", 8.0), ("overflow", 16.0)])
+@pytest.mark.parametrize("H", [2, 80])
+def test_growing_scores_in_both_forms(H, D, causal, regime, jump):
+    """Scores that grow along the sequence with 2 heads (split keys) and with
+    80 copies of them (640 items for one pattern alone: 128-row items)."""
+    note(f"[split] {regime} H={H} D={D} causal={causal}")
+    q, k, v = (x.repeat(1, 1, H // 2, 1) for x in _integer_qkv(1, 1000, 2, D, seed=31 + D, jump_at=300, jump=jump))
+    compare_full(q, k, v, [(1000, 1), (500, 2)], causal, "bf16", scale=REGIME_SCALES["generic"] / LOG2E,
+                 tag=f"{regime} H{H} D{D}", heads=[0, 1])
+
+
+@pytest.mark.parametrize("H", [17, 136])
+def test_wide_row_stride_in_both_forms(H):
+    """64-bit addressing (key tiles spanning 2 GiB) in both forms."""
+    note(f"[split] wide stride H={H}")
+    r = -(-65536 // H)  # r * H * 128 columns * 2 bytes * 129 rows >= 2^31
+    N = 5 * r
+    q, k, v = (workloads.make_random((1, N, H, 128), torch.bfloat16, 1.0, 310, "cuda", t) for t in range(3))
+    pats = [(N, r)] * (1 if H == 17 else 4)
+    compare_full(q, k, v, pats, True, "bf16", tag=f"wide H{H}", heads=[0, H - 1])
