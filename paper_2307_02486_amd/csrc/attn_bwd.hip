@@ -124,6 +124,38 @@ struct TileLoader {
   }
 };
 
+// Stores a wave's 32 gradient rows (row r0 + lane % 32 in the lane's
+// accumulators, C layout) as fp16 times the row's factor per column chunk:
+// staged in LDS (32 D fp16 of the wave's own at stg) so that the stores write
+// whole rows, 16 bytes per lane.  Staged 16-byte chunk x of row k sits at chunk
+// x ^ ((k >> 1) mod D/8), as in the forward's epilogue.  `rows` = rows before
+// the segment's end.
+template <int D>
+__device__ inline void store_grad_rows(char* stg, const f32x16 (&acc)[D / 32], const float (&mul)[kChunks<D>],
+                                       _Float16* out, int rows, int lane) {
+  using TL = TileLayout<D>;
+  const int qr = lane & 31, hi = lane >> 5;
+  auto stg_off = [&](int row, int chunk) {
+    return row * TL::kRowBytes + ((chunk ^ ((row >> 1) & (TL::kSlots - 1))) << 4);
+  };
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const float m = mul[db * 32 / kCols<D>];
+      f16x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = (_Float16)(acc[db][4 * jj + e] * m);
+      *reinterpret_cast<f16x4*>(stg + stg_off(qr, db * 4 + jj) + 8 * hi) = o;
+    }
+#pragma unroll
+  for (int i = 0; i < 32 * TL::kRowBytes / 1024; ++i) {
+    const int row = (i * 64 + lane) / TL::kSlots, chunk = (i * 64 + lane) % TL::kSlots;
+    const u32x4 x = *reinterpret_cast<const u32x4*>(stg + stg_off(row, chunk));
+    if (row < rows) *reinterpret_cast<u32x4*>(out + row * D + chunk * 8) = x;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // bwd_delta: -delta = -sum_d dout*out and -lse/scale, per (b, h, p).
 // ---------------------------------------------------------------------------
@@ -342,22 +374,13 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
     amax = fmaxf(amax, other_half(amax));
     row_scale(amax * a.scale, a.scale, mul[ch], rs[ch]);
   }
-  if (!q_valid) return;
-  const int64_t wrow = (int64_t)it.unit * P.lmax + tq_row;
-  _Float16* orow = reinterpret_cast<_Float16*>(a.ws + P.dq_off) + wrow * D;
-#pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      const float m = mul[db / CB];
-      *reinterpret_cast<f16x4*>(orow + db * 32 + 8 * jj + 4 * hi) =
-          f16x4{(_Float16)(acc_dq[db][4 * jj] * m), (_Float16)(acc_dq[db][4 * jj + 1] * m),
-                (_Float16)(acc_dq[db][4 * jj + 2] * m), (_Float16)(acc_dq[db][4 * jj + 3] * m)};
-    }
-  if (hi == 0)
+  const int64_t wrow0 = (int64_t)it.unit * P.lmax + wq_lo;  // the wave's first compact row
+  store_grad_rows<D>(reinterpret_cast<char*>(&sm.a[0][0]) + wv * 32 * TL::kRowBytes, acc_dq, mul,
+                     reinterpret_cast<_Float16*>(a.ws + P.dq_off) + wrow0 * D, L - wq_lo, lane);
+  if (hi == 0 && q_valid)
 #pragma unroll
     for (int ch = 0; ch < kChunks<D>; ++ch)
-      reinterpret_cast<float*>(a.ws + P.dq_rec_off)[wrow * kChunks<D> + ch] = rs[ch];
+      reinterpret_cast<float*>(a.ws + P.dq_rec_off)[(wrow0 + qr) * kChunks<D> + ch] = rs[ch];
 }
 
 // ---------------------------------------------------------------------------
@@ -537,28 +560,17 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dkdv(BwdArgs a) {
     }
   amax_k = fmaxf(amax_k, other_half(amax_k));
   amax_v = fmaxf(amax_v, other_half(amax_v));
-  if (!k_valid) return;
-  float mul_k, rs_k, mul_v, rs_v;
-  row_scale(amax_k * a.scale, a.scale, mul_k, rs_k);
-  row_scale(amax_v, 1.0f, mul_v, rs_v);
-  const int64_t wrow = (int64_t)it.unit * P.lmax + tk_row;
-  _Float16* krow_out = reinterpret_cast<_Float16*>(a.ws + P.dk_off) + wrow * D;
-  _Float16* vrow_out = reinterpret_cast<_Float16*>(a.ws + P.dv_off) + wrow * D;
-#pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      const int d = db * 32 + 8 * jj + 4 * hi;
-      *reinterpret_cast<f16x4*>(krow_out + d) =
-          f16x4{(_Float16)(acc_dk[db][4 * jj] * mul_k), (_Float16)(acc_dk[db][4 * jj + 1] * mul_k),
-                (_Float16)(acc_dk[db][4 * jj + 2] * mul_k), (_Float16)(acc_dk[db][4 * jj + 3] * mul_k)};
-      *reinterpret_cast<f16x4*>(vrow_out + d) =
-          f16x4{(_Float16)(acc_dv[db][4 * jj] * mul_v), (_Float16)(acc_dv[db][4 * jj + 1] * mul_v),
-                (_Float16)(acc_dv[db][4 * jj + 2] * mul_v), (_Float16)(acc_dv[db][4 * jj + 3] * mul_v)};
-    }
-  if (hi == 0) {
-    reinterpret_cast<float*>(a.ws + P.dk_rec_off)[wrow] = rs_k;
-    reinterpret_cast<float*>(a.ws + P.dv_rec_off)[wrow] = rs_v;
+  float mul_k[1], rs_k, mul_v[1], rs_v;
+  row_scale(amax_k * a.scale, a.scale, mul_k[0], rs_k);
+  row_scale(amax_v, 1.0f, mul_v[0], rs_v);
+  const int64_t wrow0 = (int64_t)it.unit * P.lmax + kw0;  // the wave's first compact row
+  char* stg = reinterpret_cast<char*>(&sm.a[0][0]) + wv * 64 * TL::kRowBytes;
+  store_grad_rows<D>(stg, acc_dk, mul_k, reinterpret_cast<_Float16*>(a.ws + P.dk_off) + wrow0 * D, L - kw0, lane);
+  store_grad_rows<D>(stg + 32 * TL::kRowBytes, acc_dv, mul_v, reinterpret_cast<_Float16*>(a.ws + P.dv_off) + wrow0 * D,
+                     L - kw0, lane);
+  if (hi == 0 && k_valid) {
+    reinterpret_cast<float*>(a.ws + P.dk_rec_off)[wrow0 + kr] = rs_k;
+    reinterpret_cast<float*>(a.ws + P.dv_rec_off)[wrow0 + kr] = rs_v;
   }
 }
 
@@ -786,28 +798,17 @@ __global__ __launch_bounds__(kThreadsB, 2) void bwd_dkdv_wide(BwdArgs a) {
     row_scale(amax_k * a.scale, a.scale, mul_k[ch], rs_k[ch]);
     row_scale(amax_v, 1.0f, mul_v[ch], rs_v[ch]);
   }
-  if (!k_valid) return;
-  const int64_t wrow = (int64_t)it.unit * P.lmax + tk_row;
-  _Float16* krow_out = reinterpret_cast<_Float16*>(a.ws + P.dk_off) + wrow * D;
-  _Float16* vrow_out = reinterpret_cast<_Float16*>(a.ws + P.dv_off) + wrow * D;
-#pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      const int d = db * 32 + 8 * jj + 4 * hi;
-      const float mk = mul_k[db / CB], mv = mul_v[db / CB];
-      *reinterpret_cast<f16x4*>(krow_out + d) =
-          f16x4{(_Float16)(acc_dk[db][4 * jj] * mk), (_Float16)(acc_dk[db][4 * jj + 1] * mk),
-                (_Float16)(acc_dk[db][4 * jj + 2] * mk), (_Float16)(acc_dk[db][4 * jj + 3] * mk)};
-      *reinterpret_cast<f16x4*>(vrow_out + d) =
-          f16x4{(_Float16)(acc_dv[db][4 * jj] * mv), (_Float16)(acc_dv[db][4 * jj + 1] * mv),
-                (_Float16)(acc_dv[db][4 * jj + 2] * mv), (_Float16)(acc_dv[db][4 * jj + 3] * mv)};
-    }
-  if (hi == 0)
+  const int64_t wrow0 = (int64_t)it.unit * P.lmax + kw0;  // the wave's first compact row
+  char* stg = reinterpret_cast<char*>(&sm) + wv * 64 * TL::kRowBytes;
+  static_assert(4 * 64 * TL::kRowBytes <= sizeof(sm.v) + sizeof(sm.a) + sizeof(sm.b), "fits V and the tiles");
+  store_grad_rows<D>(stg, acc_dk, mul_k, reinterpret_cast<_Float16*>(a.ws + P.dk_off) + wrow0 * D, L - kw0, lane);
+  store_grad_rows<D>(stg + 32 * TL::kRowBytes, acc_dv, mul_v, reinterpret_cast<_Float16*>(a.ws + P.dv_off) + wrow0 * D,
+                     L - kw0, lane);
+  if (hi == 0 && k_valid)
 #pragma unroll
     for (int ch = 0; ch < kChunks<D>; ++ch) {
-      reinterpret_cast<float*>(a.ws + P.dk_rec_off)[wrow * kChunks<D> + ch] = rs_k[ch];
-      reinterpret_cast<float*>(a.ws + P.dv_rec_off)[wrow * kChunks<D> + ch] = rs_v[ch];
+      reinterpret_cast<float*>(a.ws + P.dk_rec_off)[(wrow0 + kr) * kChunks<D> + ch] = rs_k[ch];
+      reinterpret_cast<float*>(a.ws + P.dv_rec_off)[(wrow0 + kr) * kChunks<D> + ch] = rs_v[ch];
     }
 }
 
