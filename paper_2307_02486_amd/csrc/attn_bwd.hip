@@ -12,7 +12,8 @@
 // applied to the fp32 sum (P = exp2(scale log2(e) (q.k - lse / scale))), so q
 // and k enter the MFMAs as given.
 // Four kernels:
-//   bwd_delta  per row: -delta and -lse/scale into the workspace;
+//   bwd_delta  per row: -delta and -lse/scale into the workspace, where no
+//              pattern keeps every row (r = 1) and its dq items write them;
 //   bwd_dq     per (pattern, segment, 128-query tile): each lane owns a query;
 //              over the segment's key tiles, S^T = K Q^T and (dP - delta)^T =
 //              V dO^T start from -lse and -delta (no running max: lse is
@@ -50,12 +51,15 @@ struct BwdArgs {
   const void* k;
   const void* v;
   const void* dout;
-  const float* nl2;  // -lse / scale, [B][H][N]: the score offset before the scale
-  const float* nd;   // -delta, [B][H][N]
+  const void* out;
+  const float* lse;
+  float* nl2;  // -lse / scale, [B][H][N]: the score offset before the scale
+  float* nd;   // -delta, [B][H][N]
   char* ws;
   int32_t B, N, H, npat, causal;
-  float scale_log2;  // softmax scale * log2(e)
-  float scale;
+  int32_t delta_pat;  // pattern whose dq items write nl2 and nd (it keeps every row), or -1
+  float scale_log2;   // softmax scale * log2(e)
+  float scale, inv_scale;
   BwdPat pat[DA_MAX_PATTERNS];  // by query tiles per unit, most first
 };
 
@@ -257,7 +261,26 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
   // The scores start from -lse/scale where registers allow (D <= 64), and from
   // zero with -lse added beside the scale otherwise.
   constexpr bool kLseInit = D <= 64;
-  const float nl2 = a.nl2[srow], nd = a.nd[srow];
+  float nd;
+  {
+    // delta of this lane's query: the half-waves hold complementary slices
+    const u16* op = static_cast<const u16*>(a.out) + qoff + 8 * hi;
+    u32x4 oraw[KC];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) oraw[c] = load16(op + 16 * c);
+    float d = 0.0f;
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        d += __builtin_bit_cast(float, (oraw[c][e >> 1] >> (16 * (e & 1))) << 16) * static_cast<float>(doreg[c][e]);
+    nd = -(d + other_half(d));
+  }
+  const float nl2 = -a.lse[srow] * a.inv_scale;
+  if (it.pi == a.delta_pat && hi == 0 && q_valid) {
+    a.nl2[srow] = nl2;
+    a.nd[srow] = nd;
+  }
   const float nl = nl2 * a.scale_log2;  // -lse in log2 units
   f32x16 vs0, vnd;
 #pragma unroll
@@ -913,8 +936,11 @@ hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q
   a.k = k;
   a.v = v;
   a.dout = dout;
+  a.out = out;
+  a.lse = lse;
   a.nl2 = da_.nl2;
   a.nd = da_.nd;
+  a.inv_scale = da_.inv_scale;
   a.ws = ws;
   a.B = static_cast<int32_t>(plan.B);
   a.N = static_cast<int32_t>(plan.N);
@@ -957,11 +983,21 @@ hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q
       sp = SumPat{make_fastdiv(1), make_fastdiv(1), 1, 1, 0, 0, 0, 0, 0, 0};
     }
   }
+  // Every dq item forms its rows' delta from dO, which it holds, and their out
+  // rows; those of a pattern with r = 1 cover every row once and write delta
+  // and -lse/scale for the dk/dv kernel, which saves a launch and a pass over
+  // out and dout: 934 -> 931 us at 32K tokens (H = 12, D = 64, five patterns),
+  // where most of the pass's 20 us comes back as reads of out rows in the dq
+  // items; 46.4 -> 43.4 at N = 8192, H = 8, D = 32, 92.1 -> 90.7 at N = 2048.
+  a.delta_pat = -1;
+  for (int i = plan.npat - 1; i >= 0; --i)
+    if (plan.pat[order[i]].r == 1) a.delta_pat = i;
+  const bool delta = a.delta_pat < 0;
   const dim3 rgrid(static_cast<unsigned>(rblocks));
   const dim3 igrid(static_cast<unsigned>(plan.launch_items));
   switch (plan.D) {
     case 32:
-      hipLaunchKernelGGL(bwd_delta<32>, rgrid, dim3(kThreadsB), 0, stream, da_);
+      if (delta) hipLaunchKernelGGL(bwd_delta<32>, rgrid, dim3(kThreadsB), 0, stream, da_);
       if (plan.total_items > 0) {
         hipLaunchKernelGGL(bwd_dq<32>, igrid, dim3(kThreadsB), 0, stream, a);
         hipLaunchKernelGGL(bwd_dkdv<32>, igrid, dim3(kThreadsB), 0, stream, a);
@@ -969,7 +1005,7 @@ hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q
       hipLaunchKernelGGL(bwd_sum<32>, rgrid, dim3(kThreadsB), 0, stream, sa);
       break;
     case 64:
-      hipLaunchKernelGGL(bwd_delta<64>, rgrid, dim3(kThreadsB), 0, stream, da_);
+      if (delta) hipLaunchKernelGGL(bwd_delta<64>, rgrid, dim3(kThreadsB), 0, stream, da_);
       if (plan.total_items > 0) {
         hipLaunchKernelGGL(bwd_dq<64>, igrid, dim3(kThreadsB), 0, stream, a);
         hipLaunchKernelGGL(bwd_dkdv<64>, igrid, dim3(kThreadsB), 0, stream, a);
@@ -977,7 +1013,7 @@ hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q
       hipLaunchKernelGGL(bwd_sum<64>, rgrid, dim3(kThreadsB), 0, stream, sa);
       break;
     case 128:
-      hipLaunchKernelGGL(bwd_delta<128>, rgrid, dim3(kThreadsB), 0, stream, da_);
+      if (delta) hipLaunchKernelGGL(bwd_delta<128>, rgrid, dim3(kThreadsB), 0, stream, da_);
       if (plan.total_items > 0) {
         hipLaunchKernelGGL(bwd_dq<128>, igrid, dim3(kThreadsB), 0, stream, a);
         hipLaunchKernelGGL(bwd_dkdv_wide<128>, igrid, dim3(kThreadsB), 0, stream, a);
