@@ -33,3 +33,30 @@ def test_no_grad_forward_is_the_same(dtype, use_xpos, strided):
     assert torch.equal(got, want) and torch.equal(x, before)
     with torch.inference_mode():
         assert torch.equal(layer(x), want)
+
+
+@pytest.mark.parametrize("dtype,E", [(torch.float32, 64), (torch.bfloat16, 128)], ids=str)
+@pytest.mark.parametrize("frozen", [(), ("x",), (2, 3), (0, 1, 2, 3, 4, 5), ("x", 4, 5)], ids=str)
+def test_qkv_gradients_match_single_projections(dtype, E, frozen):
+    """One function for the three projections against three, with some of the
+    input and the parameters (weight, bias of q, k, v) frozen.  The parameter
+    gradients are the same products (the same bits); the input's is summed in
+    another order: float32 within 1e-5 of its largest entry, bf16 within 2^-7
+    (two roundings of 2^-9 on either side)."""
+    from paper_2307_02486_amd.layer import LinearFunction, QKVFunction
+    note(f"[qkv] {dtype} frozen={frozen}")
+    x = workloads.make_random((2, 75, E), dtype, 1.0, 71, "cuda", 0).requires_grad_("x" not in frozen)
+    params = [workloads.make_random((E, E) if i % 2 == 0 else (E,), dtype, E ** -0.5, 72, "cuda", i)
+              .requires_grad_(i not in frozen) for i in range(6)]
+    dys = [workloads.make_random((2, 75, E), dtype, 1.0, 73, "cuda", i) for i in range(3)]
+    leaves = [t for t in (x, *params) if t.requires_grad]
+    got = torch.autograd.grad(QKVFunction.apply(x, *params), leaves, dys, allow_unused=True) if leaves else ()
+    outs = [LinearFunction.apply(x, params[2 * i], params[2 * i + 1]) for i in range(3)]
+    keep = [i for i in range(3) if outs[i].requires_grad]
+    want = torch.autograd.grad([outs[i] for i in keep], leaves, [dys[i] for i in keep], allow_unused=True)
+    for leaf, g, w in zip(leaves, got, want):
+        if leaf is x:
+            tol = (1e-5 if dtype == torch.float32 else 2.0 ** -7) * float(w.abs().max())
+            assert float((g.float() - w.float()).abs().max()) <= tol
+        else:
+            assert torch.equal(g, w)
