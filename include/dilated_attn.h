@@ -68,7 +68,8 @@ enum {
 typedef struct {
   uint64_t workspace_bytes; /* device memory the caller passes to fwd        */
   int64_t num_work_items;   /* attention work items (pattern, b, h, segment,
-                               query tile) launched by fwd                    */
+                               query tile of 128 rows, or 64 in float32;
+                               small bf16 launches cut them in two)           */
   int64_t covered_rows;     /* sum over patterns of kept (b, row, head) rows  */
   double sparse_flops;      /* 4*D per unmasked (query, key) pair, the work of
                                Sec. 2.4 counted exactly                       */
@@ -173,7 +174,7 @@ int dilated_attn_fwd_noalloc(const void* q, const void* k, const void* v, void* 
  * the dk/dv kernels' work items, covered_rows, sparse_flops = 10*D per
  * unmasked (query, key) pair (the five products of the derivative),
  * bytes_attn = algorithmic HBM bytes of the two gradient kernels and
- * bytes_combine = those of the delta and gradient-sum kernels.
+ * bytes_combine = those of the delta pass and the gradient-sum kernel.
  */
 int dilated_attn_bwd_plan(int64_t B, int64_t N, int64_t H, int64_t D,
                           const da_pattern_t* patterns, int64_t num_patterns,
@@ -267,8 +268,8 @@ int dilated_attn_xpos(const void* x, void* y, int64_t B, int64_t N, int64_t H, i
  *             ignored, on return unspecified.
  * stream      a hipStream_t (NULL = the default stream); asynchronous.
  *
- * Products and sums in float32 (matrix cores; db on the vector units, summed
- * per 256-row slice and then over the slices), rounded to bf16 once.
+ * Products and sums in float32 (matrix cores, per chunk of rows and then over
+ * the chunks), rounded to bf16 once.
  * All device pointers 16-byte aligned.  Returns DA_OK or a negative code;
  * errors launch nothing.
  */

@@ -37,7 +37,7 @@ hipError_t launch_attention(const Plan& plan, const void* q, const void* k, cons
 hipError_t launch_combine(const Plan& plan, const void* workspace, void* out, float* lse,
                           hipStream_t stream);
 
-// Backward: per-row -delta and -lse*log2(e), the per-pattern dq and dk/dv
+// Backward: per-row -delta and -lse/scale, the per-pattern dq and dk/dv
 // kernels into compact workspace rows, and their sum per row into dq, dk, dv.
 hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q, const void* k,
                            const void* v, const void* out, const float* lse, const void* dout, void* dq,

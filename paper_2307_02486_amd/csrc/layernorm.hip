@@ -274,18 +274,22 @@ __global__ __launch_bounds__(kLnThreads) void ln_reduce(const float* part, u16* 
 
 }  // namespace
 
-// Rows per wave of the backward: at most 768 workgroups (three per CU, all
-// resident at once at any width), one partial of 2E floats each.
-static int64_t ln_rows_per_wave(int64_t rows) { return std::max<int64_t>(1, (rows + 3071) / 3072); }
-static int64_t ln_bwd_workgroups(int64_t rows) {
-  const int64_t per_wg = ln_rows_per_wave(rows) * (kLnThreads / 64);
-  return (rows + per_wg - 1) / per_wg;
+// Partials that the workspace holds: one per 32 rows and one more per 1024.
+static int64_t ln_partials(int64_t rows) {
+  const int64_t blocks = (rows + 31) / 32;
+  return blocks + (blocks + 31) / 32;
 }
 
-// At least one partial per 32 rows and one more per 1024.
+// Rows per wave of the backward: at most 768 workgroups (three per CU, all
+// resident at once at any width), and no more than the workspace has partials
+// for.
+static int64_t ln_rows_per_wave(int64_t rows) {
+  const int64_t waves = std::min<int64_t>(768, std::max<int64_t>(1, ln_partials(rows))) * (kLnThreads / 64);
+  return std::max<int64_t>(1, (rows + waves - 1) / waves);
+}
+
 uint64_t layernorm_bwd_workspace(int64_t rows, int64_t E) {
-  const int64_t blocks = (rows + 31) / 32;
-  return static_cast<uint64_t>(std::max(blocks + (blocks + 31) / 32, ln_bwd_workgroups(rows))) * 2 * E * 4;
+  return static_cast<uint64_t>(ln_partials(rows)) * 2 * E * 4;
 }
 
 hipError_t launch_layernorm_fwd(const void* x, const void* g, const void* b, void* y, float* mean, float* rstd,
@@ -304,11 +308,13 @@ hipError_t launch_layernorm_fwd(const void* x, const void* g, const void* b, voi
 hipError_t launch_layernorm_bwd(const void* dy, const void* x, const void* g, const float* mean, const float* rstd,
                                 void* dx, void* dg, void* db, int64_t rows, int64_t E, void* workspace,
                                 hipStream_t stream) {
-  const int64_t nwg = ln_bwd_workgroups(rows);
+  const int64_t rpw = ln_rows_per_wave(rows);
+  const int64_t per_wg = rpw * (kLnThreads / 64);
+  const int64_t nwg = (rows + per_wg - 1) / per_wg;
   float* part = static_cast<float*>(workspace);
   LnBwdArgs a{static_cast<const u16*>(dy), static_cast<const u16*>(x), static_cast<const u16*>(g), mean, rstd,
               static_cast<u16*>(dx), part, rows, static_cast<int32_t>(E),
-              static_cast<int32_t>(ln_rows_per_wave(rows))};
+              static_cast<int32_t>(rpw)};
   const dim3 grid(static_cast<unsigned>(nwg));
   const size_t smem = static_cast<size_t>(kLnThreads / 64) * 2 * E * sizeof(float);
   if (nwg > 0) {  // no rows: only the reduction, which then writes zeros

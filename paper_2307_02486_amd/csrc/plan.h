@@ -66,11 +66,11 @@ struct Plan {
   double bytes_combine;
 };
 
-// Workspace of a backward call: per (b, h, row) -lse*log2(e) and -delta
-// (float32, [B][H][N] each), then per pattern the compact float32 gradients
+// Workspace of a backward call: per (b, h, row) -lse/scale and -delta
+// (float32, [B][H][N] each), then per pattern the compact fp16 gradients
 // of its kept rows, [units][lmax][D] for dq, dk and dv.
 struct BwdLayout {
-  uint64_t nl2_off;   // byte offset of -lse*log2(e)
+  uint64_t nl2_off;   // byte offset of -lse/scale
   uint64_t nd_off;    // byte offset of -delta
   // Per pattern, the compact gradients dq, dk, dv: fp16 rows [units*lmax][D],
   // each row scaled by a power of two per chunk of kGradChunk columns, and
