@@ -28,10 +28,12 @@ from .ops import dilated_attn, dilated_attn_bwd, layer_norm, layer_norm_bwd, wgr
 
 def _plain() -> bool:
     """Whether nothing records or transforms the operations: no gradients, no
-    forward-mode level, no functorch transform.  The layer then calls the
-    kernels without the autograd functions (which cost 5 us of host time each:
-    of a 2K-token forward's 194 us on the host, 40)."""
-    return not (torch.is_grad_enabled() or forward_ad._current_level >= 0
+    trace (torch.jit.trace keeps the autograd functions as calls, and sees
+    nothing of a kernel called past them), no forward-mode level, no functorch
+    transform.  The layer then calls the kernels without the autograd functions
+    (which cost 5 us of host time each: of a 2K-token forward's 194 us on the
+    host, 40)."""
+    return not (torch.is_grad_enabled() or torch.jit.is_tracing() or forward_ad._current_level >= 0
                 or torch._C._are_functorch_transforms_active())
 
 

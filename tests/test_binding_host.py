@@ -1,5 +1,8 @@
 """The binding's per-call look-ups and the layer's choice of the path without
 autograd functions (no GPU needed)."""
+import ctypes
+
+import numpy as np
 import pytest
 import torch
 from torch.autograd import forward_ad
@@ -43,3 +46,45 @@ def test_plain_only_without_recording_or_transforms():
         assert seen == [False]
     with torch.inference_mode():
         assert _plain()
+
+
+def _stand_ins(monkeypatch):
+    """CPU stand-ins for the layer's attention and xPos kernels that write their
+    results through raw pointers, as the library does."""
+    from paper_2307_02486_amd import layer
+
+    def array(t):
+        return np.ctypeslib.as_array(ctypes.cast(t.data_ptr(), ctypes.POINTER(ctypes.c_float)), tuple(t.shape))
+
+    def xpos(x, sign, transpose=False, center=None, base=0.0, gamma=0.0, scale_base=0.0, out=None):
+        out = torch.empty_like(x) if out is None else out
+        array(out)[...] = array(x) * (1.0 + 0.5 * sign)
+        return out
+
+    def dilated_attn(q, k, v, patterns, causal, scale=None):
+        out, lse = torch.empty_like(q), torch.empty(q.shape[0], q.shape[2], q.shape[1])
+        array(out)[...] = array(q) * array(k) + array(v)
+        array(lse)[...] = 0.0
+        return out, lse
+
+    monkeypatch.setattr(layer, "xpos", xpos)
+    monkeypatch.setattr(layer, "dilated_attn", dilated_attn)
+
+
+@pytest.mark.parametrize("record", ["no_grad", "inference", "grad"])
+def test_traced_layer_replays_on_new_inputs(record, monkeypatch):
+    """A trace holds the layer's kernel calls whatever the gradient mode: kernels
+    called past the autograd functions write through pointers the tracer does
+    not see, and the replay would return uninitialised memory."""
+    from paper_2307_02486_amd.layer import LongNetAttention
+    _stand_ins(monkeypatch)
+    torch.manual_seed(3)
+    layer = LongNetAttention(64, 2, [(8, 1), (16, 2)], dtype=torch.float32, device="cpu")
+    x0, x1 = torch.randn(2, 16, 64), torch.randn(2, 16, 64)
+    mode = {"no_grad": torch.no_grad, "inference": torch.inference_mode, "grad": torch.enable_grad}[record]
+    with mode():
+        traced = torch.jit.trace(layer, x0, check_trace=False)
+    with torch.no_grad():
+        want = layer(x1)
+        assert torch.equal(traced(x1), want) and torch.equal(traced(x0), layer(x0))
+        assert not torch.equal(traced(x0), want)
