@@ -225,7 +225,7 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
   __shared__ SmemTiles<D> sm;
 
   Item it;
-  if (!decode_item(a, __builtin_amdgcn_workgroup_id_x(), kTileB, it)) return;
+  if (!decode_item(a, launch_index(), kTileB, it)) return;
   const BwdPat& P = a.pat[it.pi];
   const int tid = __builtin_amdgcn_workitem_id_x();
   const int lane = tid & 63;
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dkdv(BwdArgs a) {
   __shared__ SmemTiles<D> sm;
 
   Item it;
-  if (!decode_item(a, __builtin_amdgcn_workgroup_id_x(), 0, it)) return;
+  if (!decode_item(a, launch_index(), 0, it)) return;
   const BwdPat& P = a.pat[it.pi];
   const int kt_idx = P.ntiles - 1 - it.tq;  // longest (first) key tiles first
   const int L = it.L;
@@ -632,7 +632,7 @@ __global__ __launch_bounds__(kThreadsB, 2) void bwd_dkdv_wide(BwdArgs a) {
   __shared__ SmemWide<D> sm;
 
   Item it;
-  if (!decode_item(a, __builtin_amdgcn_workgroup_id_x(), 0, it)) return;
+  if (!decode_item(a, launch_index(), 0, it)) return;
   const BwdPat& P = a.pat[it.pi];
   const int kt_idx = P.ntiles - 1 - it.tq;  // longest (first) key tiles first
   const int L = it.L;
@@ -994,7 +994,7 @@ hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q
     if (plan.pat[order[i]].r == 1) a.delta_pat = i;
   const bool delta = a.delta_pat < 0;
   const dim3 rgrid(static_cast<unsigned>(rblocks));
-  const dim3 igrid(static_cast<unsigned>(plan.launch_items));
+  const dim3 igrid = grid_of(plan.launch_items);
   switch (plan.D) {
     case 32:
       if (delta) hipLaunchKernelGGL(bwd_delta<32>, rgrid, dim3(kThreadsB), 0, stream, da_);

@@ -89,7 +89,7 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_bf16(AttnArgs a) {
   __shared__ SmemBf16<D> sm;
 
   Item it;
-  if (!decode_item(a, __builtin_amdgcn_workgroup_id_x(), BM, it)) return;
+  if (!decode_item(a, launch_index(), BM, it)) return;
   const PatArgs& P = a.pat[it.pi];
   const u16* __restrict__ qg = static_cast<const u16*>(a.q);
 
@@ -484,7 +484,7 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_f32(AttnArgs a) {
   __shared__ SmemF32<D> sm;
 
   Item it;
-  if (!decode_item(a, __builtin_amdgcn_workgroup_id_x(), kBM32, it)) return;
+  if (!decode_item(a, launch_index(), kBM32, it)) return;
   const PatArgs& P = a.pat[it.pi];
   const int tid = __builtin_amdgcn_workitem_id_x();
   const int lane = tid & 63;
@@ -731,7 +731,7 @@ hipError_t launch_attention(const Plan& plan, const void* q, const void* k, cons
   }
   a.total_items = static_cast<int32_t>(items);
   if (items == 0) return hipSuccess;
-  const dim3 grid(static_cast<unsigned>(launch));
+  const dim3 grid = grid_of(launch);
   if (plan.dtype == DA_BF16) {
     switch (plan.D) {
       case 32:

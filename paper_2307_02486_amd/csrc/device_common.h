@@ -26,6 +26,11 @@ typedef unsigned short u16;
 constexpr float kLn2 = 0.693147180559945309f;
 constexpr float kLog2e = 1.442695040888963407f;
 
+// This workgroup's place in a launch over grid_of().
+__device__ inline int launch_index() {
+  return static_cast<int>(__builtin_amdgcn_workgroup_id_x() + __builtin_amdgcn_workgroup_id_y() * kGridRow);
+}
+
 struct PatArgs {
   int32_t w, r, nseg, lmax, ntiles, units;
   int64_t o_off;    // byte offset of this pattern's output rows in the workspace

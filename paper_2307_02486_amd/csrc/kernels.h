@@ -7,6 +7,17 @@
 
 namespace da {
 
+// Grids of 256-thread workgroups.  A grid dimension holds fewer than 2^32
+// work-items and a launch beyond wraps without an error: from 2^24 workgroups
+// on a launch is a grid of rows of kGridRow of them.  Its kernel takes its
+// place from launch_index() and returns where that is past the launch's end.
+// (kGridRow is a multiple of 8: the XCDs are dealt the same indices.)
+constexpr int64_t kGridRow = int64_t{1} << 20;
+inline dim3 grid_of(int64_t workgroups) {
+  if (workgroups < (int64_t{1} << 24)) return dim3(static_cast<unsigned>(workgroups));
+  return dim3(static_cast<unsigned>(kGridRow), static_cast<unsigned>((workgroups + kGridRow - 1) / kGridRow));
+}
+
 // A pattern as the combine step sees it: the divisions that map a sequence
 // position to the pattern's segment and kept-row index, and where the
 // pattern's rows sit in the workspace.

@@ -85,8 +85,7 @@ struct LnFwdArgs {
 template <int J>
 __global__ __launch_bounds__(kLnThreads) void ln_fwd(LnFwdArgs a) {
   const int lane = __builtin_amdgcn_workitem_id_x() & 63;
-  const int64_t row = static_cast<int64_t>(__builtin_amdgcn_workgroup_id_x()) * (kLnThreads / 64) +
-                      (__builtin_amdgcn_workitem_id_x() >> 6);
+  const int64_t row = static_cast<int64_t>(launch_index()) * (kLnThreads / 64) + (__builtin_amdgcn_workitem_id_x() >> 6);
   if (row >= a.rows) return;  // whole waves only; the kernel has no barrier
   const int nch = a.E >> 3;
   const u16* xr = a.x + row * a.E;
@@ -297,7 +296,7 @@ hipError_t launch_layernorm_fwd(const void* x, const void* g, const void* b, voi
   LnFwdArgs a{static_cast<const u16*>(x), static_cast<const u16*>(g), static_cast<const u16*>(b),
               static_cast<u16*>(y), mean, rstd, rows, static_cast<int32_t>(E), eps};
   if (rows == 0) return hipSuccess;
-  const dim3 grid(static_cast<unsigned>((rows + 3) / 4));
+  const dim3 grid = grid_of((rows + 3) / 4);
   const int J = static_cast<int>((E / 8 + 63) / 64);
   if (J == 1) hipLaunchKernelGGL(ln_fwd<1>, grid, dim3(kLnThreads), 0, stream, a);
   else if (J == 2) hipLaunchKernelGGL(ln_fwd<2>, grid, dim3(kLnThreads), 0, stream, a);
