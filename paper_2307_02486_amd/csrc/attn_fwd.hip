@@ -264,14 +264,19 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_bf16(AttnArgs a) {
         for (int kb = 0; kb < SB; ++kb)
 #pragma unroll
           for (int j = 0; j < 16; j += 2) mx = fmaxf(mx, fmaxf(acc_s[kb][j], acc_s[kb][j + 1]));
-        mx = fmaxf(mx, other_half(mx)) * c - m_run;  // log2 units, relative to m_run
-        // The first tile fixes the reference max; in the safe mode later tiles
-        // move it only when some row of the wave would see probabilities above
-        // 2^kRescaleSlack.
-        if (jt == 0 || __any(mx > kRescaleSlack)) {
-          const float delta = jt == 0 ? mx : fmaxf(mx, 0.0f);
-          const float alpha = __builtin_amdgcn_exp2f(-delta);
-          m_run += delta;
+        mx = fmaxf(mx, other_half(mx)) * c;  // log2 units
+        // The first tile fixes the reference max (nothing is accumulated yet);
+        // in the safe mode later tiles move it only when some row of the wave
+        // would see probabilities above 2^kRescaleSlack.  The floor keeps it
+        // finite for a row whose keys so far all scored minus infinity: their
+        // probabilities are then zero, and its first finite score moves the
+        // reference (through a safe rerun).
+        if (jt == 0) {
+          m_run = fmaxf(mx, kNegBig);
+        } else if (__any(mx - m_run > kRescaleSlack)) {
+          const float m_new = fmaxf(m_run, mx);
+          const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+          m_run = m_new;
           l_run *= alpha;
 #pragma unroll
           for (int db = 0; db < DB; ++db)

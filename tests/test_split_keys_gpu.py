@@ -50,3 +50,36 @@ def test_wide_row_stride_in_both_forms(H):
     q, k, v = (workloads.make_random((1, N, H, 128), torch.bfloat16, 1.0, 310, "cuda", t) for t in range(3))
     pats = [(N, r)] * (1 if H == 17 else 4)
     compare_full(q, k, v, pats, True, "bf16", tag=f"wide H{H}", heads=[0, H - 1])
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("causal,lost", [(True, (32, 64)), (True, (1, 64)), (True, (64, 128)), (False, (0, 32)),
+                                         (False, (32, 64)), (False, (0, 64)), (False, (0, 199))], ids=str)
+@pytest.mark.parametrize("H,offset", [(2, 0.0), (2, 32.0), (260, 0.0)])
+def test_scores_overflowing_to_minus_infinity(H, offset, causal, lost, D):
+    """q.k of the keys `lost` is -2^140, minus infinity in float32 and without
+    weight in the oracle: a wave that sees only such keys in its first block (or
+    the row's first tile) leaves the row to the others, with 2 heads (split
+    keys) and with 260 (two items of 128 rows each: 520 of them).  `offset`
+    raises the finite scores (about 370 in log2 units at D = 64): the reference
+    max is found again once a finite score is seen."""
+    N = 200
+    note(f"[split] -inf keys {lost} H={H} D={D} causal={causal} offset={offset}")
+    q, k, v = (workloads.make_random((1, N, H, D), torch.bfloat16, 1.0, 320 + D, "cuda", t) for t in range(3))
+    q[..., 0], k[..., 0] = 2.0 ** 70, 0.0
+    k[:, lost[0]:lost[1], :, 0] = -(2.0 ** 70)
+    if offset:
+        q[..., 1], k[..., 1] = 64.0, offset
+    compare_full(q, k, v, [(N, 1)], causal, "bf16", tag=f"-inf {lost} H{H} D{D}", heads=[0, H - 1])
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("H", [2, 260])
+def test_scores_far_below_zero(H, causal, D):
+    """Every score about -2048 / sqrt(D): the first tile's reference max lies
+    below -128 in log2 units, whose negative has no float32 power of two."""
+    note(f"[split] low scores H={H} D={D} causal={causal}")
+    q, k, v = (workloads.make_random((1, 200, H, D), torch.bfloat16, 1.0, 330 + D, "cuda", t) for t in range(3))
+    q[..., 1], k[..., 1] = 64.0, -32.0
+    compare_full(q, k, v, [(200, 1), (100, 2)], causal, "bf16", tag=f"low H{H} D{D}", heads=[0, H - 1])
