@@ -154,6 +154,7 @@ __global__ __launch_bounds__(kLnThreads) void ln_bwd(LnBwdArgs a) {
   const int tid = __builtin_amdgcn_workitem_id_x();
   const int lane = tid & 63, wv = tid >> 6;
   const int nch = a.E >> 2;
+  constexpr int kFull = J <= 4 ? J - 1 : J - 2;  // chunks that every lane has (see the launch)
   float g[J][4], pg[J][4], pb[J][4];
 #pragma unroll
   for (int j = 0; j < J; ++j) {
@@ -194,16 +195,19 @@ __global__ __launch_bounds__(kLnThreads) void ln_bwd(LnBwdArgs a) {
       dyr[j] = ndy[j];
     }
     if (i + 1 < nrow) load_row(row + 1);
-    // Lanes past the row's end have dy = g = 0 and add nothing.
+    // Lanes past the row's end (in the last chunks only) have dy = g = 0 and,
+    // with an rstd of zero, xhat = 0 where mean * rstd would overflow: they add
+    // nothing.
     float s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       float x[4], dy[4];
       unpack4(xr[j], x);
       unpack4(dyr[j], dy);
+      const float rj = j < kFull || lane + 64 * j < nch ? rstd : 0.0f;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float xh = (x[e] - mean) * rstd, dxh = dy[e] * g[j][e];
+        const float xh = (x[e] - mean) * rj, dxh = dy[e] * g[j][e];
         s1 += dxh;
         s2 += dxh * xh;
         pg[j][e] += dy[e] * xh;

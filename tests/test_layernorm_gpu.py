@@ -133,3 +133,25 @@ def test_layernorm_errors_launch_nothing():
 ], ids=str)
 def test_layernorm_row_and_width_variants(case):
     test_layernorm_matches_float32(case)
+
+
+@pytest.mark.parametrize("E", [64, 264, 1288, 1800])
+def test_layernorm_bwd_large_equal_entries(E):
+    """Rows of equal entries near 2e36, whose mean times rstd passes float32's
+    range: x - mean is zero, so dx = rstd (dxhat - mean(dxhat)) and dg = 0, at
+    widths whose last chunks leave lanes idle.  Bar: that of dx above, with
+    xhat = 0."""
+    from paper_2307_02486_amd import layer_norm_bwd
+    note(f"[layernorm] large equal entries E={E}")
+    _, g, _, dy = _data(37, E, 1.0, 0.0, 60 + E)
+    x = torch.full((37, E), 2e36, dtype=torch.bfloat16, device="cuda")
+    mean = x[:, 0].float().contiguous()
+    rstd = torch.full((37,), 316.0, device="cuda")
+    assert not torch.isfinite(mean * rstd).any()
+    dx, dg, db = layer_norm_bwd(dy, x, g, mean, rstd)
+    torch.cuda.synchronize()
+    dyg = dy.double() * g.double()
+    ref = 316.0 * (dyg - dyg.mean(1, keepdim=True))
+    bound = 2.0 ** -8 * ref.abs() + 2.0 ** -14 * 316.0 * dyg.abs().amax(1, keepdim=True)
+    assert float(((dx.double() - ref).abs() / bound).max()) <= 1.0
+    assert (dg == 0).all() and torch.isfinite(db).all()
