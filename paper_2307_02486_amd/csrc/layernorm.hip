@@ -283,11 +283,16 @@ static int64_t ln_partials(int64_t rows) {
   return blocks + (blocks + 31) / 32;
 }
 
-// Rows per wave of the backward: at most 768 workgroups (three per CU, all
-// resident at once at any width), and no more than the workspace has partials
-// for.
-static int64_t ln_rows_per_wave(int64_t rows) {
-  const int64_t waves = std::min<int64_t>(768, std::max<int64_t>(1, ln_partials(rows))) * (kLnThreads / 64);
+// Rows per wave of the backward: at most as many workgroups as are resident at
+// once, and no more than the workspace has partials for.  The rows a lane
+// holds set the registers: up to four chunks (E <= 1024) 154, three waves per
+// SIMD and so three workgroups per CU; six (E <= 1536) 208, two; eight 265, one.
+// Backward, us, 768 workgroups at every width -> by this rule: 24000 x 1280
+// 42 -> 37, 50000 x 1536 111 -> 102, 24000 x 1704 57 -> 47, 16384 x 2048 47 ->
+// 42, 65536 x 2048 170 -> 173; 512 at E <= 1024: 65536 x 768 55 -> 62.
+static int64_t ln_rows_per_wave(int64_t rows, int64_t E) {
+  const int64_t resident = E <= 1024 ? 768 : E <= 1536 ? 512 : 256;
+  const int64_t waves = std::min(resident, std::max<int64_t>(1, ln_partials(rows))) * (kLnThreads / 64);
   return std::max<int64_t>(1, (rows + waves - 1) / waves);
 }
 
@@ -311,7 +316,7 @@ hipError_t launch_layernorm_fwd(const void* x, const void* g, const void* b, voi
 hipError_t launch_layernorm_bwd(const void* dy, const void* x, const void* g, const float* mean, const float* rstd,
                                 void* dx, void* dg, void* db, int64_t rows, int64_t E, void* workspace,
                                 hipStream_t stream) {
-  const int64_t rpw = ln_rows_per_wave(rows);
+  const int64_t rpw = ln_rows_per_wave(rows, E);
   const int64_t per_wg = rpw * (kLnThreads / 64);
   const int64_t nwg = (rows + per_wg - 1) / per_wg;
   float* part = static_cast<float*>(workspace);

@@ -121,8 +121,9 @@ def test_layernorm_errors_launch_nothing():
 
 
 @pytest.mark.parametrize("case", [
-    # rows at which a wave takes one, two and five rows; widths of one to eight
-    # 256-element parts with the last part ragged
+    # The backward's workgroups take eight rows per wave here (one partial sum
+    # per 32 rows and one more per 1024 in the workspace), at widths of one to
+    # eight 256-element parts with the last part ragged.
     (3072, 264, 1.0, 0.0),
     (3073, 520, 1.0, 0.0),
     (12289, 248, 1.0, 0.0),
@@ -130,6 +131,23 @@ def test_layernorm_errors_launch_nothing():
     (100, 1536, 1.0, 0.0),
     (70, 1800, 1.0, 5.0),
     (5, 1024, 1.0, 0.0),
+    # one, two, four and five rows per wave
+    (8, 264, 1.0, 0.0),
+    (9, 520, 1.0, 0.0),
+    (32, 248, 1.0, 0.0),
+    (60, 1288, 1.0, 0.0),
+    # the last and the first count on either side of the limit of 768 (E <=
+    # 1024), 512 (E <= 1536) and 256 workgroups, and nine rows per wave with a
+    # ragged last wave and workgroup
+    (23808, 264, 1.0, 0.0),
+    (23809, 264, 1.0, 0.0),
+    (25000, 520, 1.0, 0.0),
+    (15872, 1288, 1.0, 0.0),
+    (15873, 1288, 1.0, 0.0),
+    (17000, 1288, 1.0, 0.0),
+    (7936, 1800, 1.0, 0.0),
+    (7937, 1800, 1.0, 0.0),
+    (9001, 1800, 1.0, 0.0),
 ], ids=str)
 def test_layernorm_row_and_width_variants(case):
     test_layernorm_matches_float32(case)
