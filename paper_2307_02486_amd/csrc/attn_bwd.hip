@@ -217,7 +217,9 @@ __global__ __launch_bounds__(kThreadsB) void bwd_delta(DeltaArgs a) {
 // patterns (2048, 1), (8192, 2), (32768, 4): 1095 us, against 1877 us when the
 // items ran once per 64-column half (40 instead of 24 MFMAs per block).
 // ---------------------------------------------------------------------------
-template <int D>
+// kDelta: delta is formed here, and the items of pattern delta_pat write it;
+// otherwise bwd_delta has written it.
+template <int D, bool kDelta>
 __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
   constexpr int BN = kStepB;
   constexpr int KC = D / 16, DB = D / 32, SB = BN / 32;
@@ -261,8 +263,8 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
   // The scores start from -lse/scale where registers allow (D <= 64), and from
   // zero with -lse added beside the scale otherwise.
   constexpr bool kLseInit = D <= 64;
-  float nd;
-  {
+  float nl2, nd;
+  if constexpr (kDelta) {
     // delta of this lane's query: the half-waves hold complementary slices
     const u16* op = static_cast<const u16*>(a.out) + qoff + 8 * hi;
     u32x4 oraw[KC];
@@ -275,11 +277,14 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
       for (int e = 0; e < 8; ++e)
         d += __builtin_bit_cast(float, (oraw[c][e >> 1] >> (16 * (e & 1))) << 16) * static_cast<float>(doreg[c][e]);
     nd = -(d + other_half(d));
-  }
-  const float nl2 = -a.lse[srow] * a.inv_scale;
-  if (it.pi == a.delta_pat && hi == 0 && q_valid) {
-    a.nl2[srow] = nl2;
-    a.nd[srow] = nd;
+    nl2 = -a.lse[srow] * a.inv_scale;
+    if (it.pi == a.delta_pat && hi == 0 && q_valid) {
+      a.nl2[srow] = nl2;
+      a.nd[srow] = nd;
+    }
+  } else {
+    nl2 = a.nl2[srow];
+    nd = a.nd[srow];
   }
   const float nl = nl2 * a.scale_log2;  // -lse in log2 units
   f32x16 vs0, vnd;
@@ -983,12 +988,16 @@ hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q
       sp = SumPat{make_fastdiv(1), make_fastdiv(1), 1, 1, 0, 0, 0, 0, 0, 0};
     }
   }
-  // Every dq item forms its rows' delta from dO, which it holds, and their out
-  // rows; those of a pattern with r = 1 cover every row once and write delta
-  // and -lse/scale for the dk/dv kernel, which saves a launch and a pass over
-  // out and dout: 934 -> 931 us at 32K tokens (H = 12, D = 64, five patterns),
-  // where most of the pass's 20 us comes back as reads of out rows in the dq
-  // items; 46.4 -> 43.4 at N = 8192, H = 8, D = 32, 92.1 -> 90.7 at N = 2048.
+  // Where a pattern keeps every row (r = 1), every dq item forms its rows'
+  // delta from dO, which it holds, and their out rows; those of that pattern
+  // write delta and -lse/scale for the dk/dv kernel, which saves a launch and a
+  // pass over out and dout: 934 -> 931 us at 32K tokens (H = 12, D = 64, five
+  // patterns), where most of the pass's 20 us comes back as reads of out rows
+  // in the dq items; 46.4 -> 43.4 at N = 8192, H = 8, D = 32, 92.1 -> 90.7 at
+  // N = 2048.  Without such a pattern the pass has to be made, and the dq items
+  // read its two scalars per row: against forming delta again, 78.6 -> 75.7 us
+  // at B = 2, N = 8192, H = 8, D = 64, patterns (1024, 2), (2048, 4), 541 -> 537
+  // at 32K tokens with four patterns from r = 2 on.
   a.delta_pat = -1;
   for (int i = plan.npat - 1; i >= 0; --i)
     if (plan.pat[order[i]].r == 1) a.delta_pat = i;
@@ -999,7 +1008,7 @@ hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q
     case 32:
       if (delta) hipLaunchKernelGGL(bwd_delta<32>, rgrid, dim3(kThreadsB), 0, stream, da_);
       if (plan.total_items > 0) {
-        hipLaunchKernelGGL(bwd_dq<32>, igrid, dim3(kThreadsB), 0, stream, a);
+        hipLaunchKernelGGL((delta ? bwd_dq<32, false> : bwd_dq<32, true>), igrid, dim3(kThreadsB), 0, stream, a);
         hipLaunchKernelGGL(bwd_dkdv<32>, igrid, dim3(kThreadsB), 0, stream, a);
       }
       hipLaunchKernelGGL(bwd_sum<32>, rgrid, dim3(kThreadsB), 0, stream, sa);
@@ -1007,7 +1016,7 @@ hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q
     case 64:
       if (delta) hipLaunchKernelGGL(bwd_delta<64>, rgrid, dim3(kThreadsB), 0, stream, da_);
       if (plan.total_items > 0) {
-        hipLaunchKernelGGL(bwd_dq<64>, igrid, dim3(kThreadsB), 0, stream, a);
+        hipLaunchKernelGGL((delta ? bwd_dq<64, false> : bwd_dq<64, true>), igrid, dim3(kThreadsB), 0, stream, a);
         hipLaunchKernelGGL(bwd_dkdv<64>, igrid, dim3(kThreadsB), 0, stream, a);
       }
       hipLaunchKernelGGL(bwd_sum<64>, rgrid, dim3(kThreadsB), 0, stream, sa);
@@ -1015,7 +1024,7 @@ hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q
     case 128:
       if (delta) hipLaunchKernelGGL(bwd_delta<128>, rgrid, dim3(kThreadsB), 0, stream, da_);
       if (plan.total_items > 0) {
-        hipLaunchKernelGGL(bwd_dq<128>, igrid, dim3(kThreadsB), 0, stream, a);
+        hipLaunchKernelGGL((delta ? bwd_dq<128, false> : bwd_dq<128, true>), igrid, dim3(kThreadsB), 0, stream, a);
         hipLaunchKernelGGL(bwd_dkdv_wide<128>, igrid, dim3(kThreadsB), 0, stream, a);
       }
       hipLaunchKernelGGL(bwd_sum<128>, rgrid, dim3(kThreadsB), 0, stream, sa);

@@ -55,9 +55,19 @@ CASES = [
     (1, 200, 5, 32, [(50, 3)], True),                    # rows no pattern keeps: zero gradients
     (1, 1031, 6, 64, [(2048, 1), (4096, 3), (333, 2)], True),  # w > N
     (1, 64, 16, 64, [(64, 64), (64, 1)], True),          # r = w
-    (1, 513, 17, 128, [(512, 1), (513, 20)], True),      # D = 128 (two column halves)
+    (1, 513, 17, 128, [(512, 1), (513, 20)], True),      # D = 128: one scale per 64 gradient columns
     (2, 777, 3, 128, [(256, 1), (512, 7), (1000, 9)], False),
-]
+    # no pattern keeps every row: delta and -lse/scale come from their own pass
+    (1, 777, 5, 32, [(256, 2), (512, 7), (1000, 9)], False),
+    (2, 777, 3, 64, [(256, 2), (512, 3), (1000, 9)], True),
+    (1, 700, 4, 64, [(300, 2), (700, 5)], False),
+    (2, 513, 3, 128, [(512, 2), (300, 3)], True),
+    (1, 777, 5, 128, [(256, 2), (777, 7)], False),
+    # the pattern that keeps every row comes last in launch order
+    (1, 1000, 3, 128, [(1000, 2), (128, 1)], True),
+    (1, 1000, 3, 64, [(1000, 2), (128, 1), (900, 3)], False),
+] + [(1, n, 2, 128, [(n, 1), (n // 2 + 1, 2)], causal)  # edges of the 32-query tiles and 128-key items
+     for n in (31, 32, 33, 65, 97, 129) for causal in (True, False)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: f"B{c[0]}N{c[1]}H{c[2]}D{c[3]}{'c' if c[5] else 'nc'}{len(c[4])}p")
