@@ -388,6 +388,7 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
     __syncthreads();
   }
 
+  if (wq_lo >= L) return;  // no row of this wave's: short segments
   // dq = scale * acc, stored scaled per column chunk (both half-waves hold
   // parts of the row: the max is exchanged before any lane leaves).
   constexpr int CB = kCols<D> / 32;  // accumulators per chunk
@@ -576,6 +577,7 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dkdv(BwdArgs a) {
     __syncthreads();
   }
 
+  if (kw0 >= L) return;  // no row of this wave's: short segments
   // dk = scale * acc_dk and dv = acc_dv, stored scaled (the row maxima are
   // exchanged before any lane leaves).
   float amax_k = 0.0f, amax_v = 0.0f;
@@ -807,6 +809,7 @@ __global__ __launch_bounds__(kThreadsB, 2) void bwd_dkdv_wide(BwdArgs a) {
     __syncthreads();
   }
 
+  if (kw0 >= L) return;  // no row of this wave's: short segments
   // dk = scale * acc_dk and dv = acc_dv, stored scaled per column chunk (the
   // row maxima are exchanged before any lane leaves).
   constexpr int CB = kCols<D> / 32;  // accumulators per chunk
