@@ -21,7 +21,7 @@
 //   bwd_dkdv   per (pattern, segment, 128-key tile): each lane owns a key;
 //              over the query tiles that see it, S = Q K^T and dP - delta =
 //              dO V^T, then dV^T += dO^T P and dK^T += Q^T dS (bwd_dkdv_wide
-//              for D = 128);
+//              for D = 128 unless the items are few);
 //   bwd_sum    per row: the compact per-pattern gradients of every pattern
 //              that keeps the row, summed and rounded to bf16.
 // The compact per-pattern gradients are fp16 rows scaled by a power of two
@@ -131,10 +131,10 @@ struct TileLoader {
 // Stores a wave's 32 gradient rows (row r0 + lane % 32 in the lane's
 // accumulators, C layout) as fp16 times the row's factor per column chunk:
 // staged in LDS (32 D fp16 of the wave's own at stg) so that the stores write
-// whole rows, 16 bytes per lane.  Staged 16-byte chunk x of row k sits at chunk
-// x ^ ((k >> 1) mod D/8), as in the forward's epilogue.  `rows` = rows before
-// the segment's end.
-template <int D>
+// whole rows (of D columns, kStride apart), 16 bytes per lane.  Staged 16-byte
+// chunk x of row k sits at chunk x ^ ((k >> 1) mod D/8), as in the forward's
+// epilogue.  `rows` = rows before the segment's end.
+template <int D, int kStride = D>
 __device__ inline void store_grad_rows(char* stg, const f32x16 (&acc)[D / 32], const float (&mul)[kChunks<D>],
                                        _Float16* out, int rows, int lane) {
   using TL = TileLayout<D>;
@@ -156,7 +156,7 @@ __device__ inline void store_grad_rows(char* stg, const f32x16 (&acc)[D / 32], c
   for (int i = 0; i < 32 * TL::kRowBytes / 1024; ++i) {
     const int row = (i * 64 + lane) / TL::kSlots, chunk = (i * 64 + lane) % TL::kSlots;
     const u32x4 x = *reinterpret_cast<const u32x4*>(stg + stg_off(row, chunk));
-    if (row < rows) *reinterpret_cast<u32x4*>(out + row * D + chunk * 8) = x;
+    if (row < rows) *reinterpret_cast<u32x4*>(out + row * kStride + chunk * 8) = x;
   }
 }
 
@@ -413,18 +413,22 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// bwd_dkdv: one work item = 128 key rows of one sparsified segment.
+// bwd_dkdv: one work item = 128 key rows of one sparsified segment; at D = 128
+// two workgroups per item, each with all scores and one half of the columns.
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(kThreadsB) void bwd_dkdv(BwdArgs a) {
   constexpr int BQ = kStepB;
-  constexpr int KC = D / 16, DB = D / 32, QB = BQ / 32;
-  static_assert(kChunks<D> == 1, "one scale per row");
+  constexpr int C = kCols<D>, kParts = kChunks<D>;  // columns per workgroup, workgroups per item
+  constexpr int KC = D / 16, DB = C / 32, QB = BQ / 32;
   using TL = TileLayout<D>;
   __shared__ SmemTiles<D> sm;
 
   Item it;
-  if (!decode_item(a, launch_index(), 0, it)) return;
+  // the parts of an item take consecutive slots of one XCD
+  const int bid = launch_index(), slot = bid >> 3;
+  const int part = kParts == 1 ? 0 : slot % kParts;
+  if (!decode_item(a, (slot / kParts) << 3 | (bid & 7), 0, it)) return;
   const BwdPat& P = a.pat[it.pi];
   const int kt_idx = P.ntiles - 1 - it.tq;  // longest (first) key tiles first
   const int L = it.L;
@@ -481,7 +485,7 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dkdv(BwdArgs a) {
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const int d = db * 32 + tr_d;
+      const int d = part * C + db * 32 + tr_d;
       vtr_off[db][t] = TL::offset(8 * t + 4 * hi + tr_r, d >> 3) + (d & 7) * 2;
     }
 
@@ -595,12 +599,13 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dkdv(BwdArgs a) {
   row_scale(amax_v, 1.0f, mul_v[0], rs_v);
   const int64_t wrow0 = (int64_t)it.unit * P.lmax + kw0;  // the wave's first compact row
   char* stg = reinterpret_cast<char*>(&sm.a[0][0]) + wv * 64 * TL::kRowBytes;
-  store_grad_rows<D>(stg, acc_dk, mul_k, reinterpret_cast<_Float16*>(a.ws + P.dk_off) + wrow0 * D, L - kw0, lane);
-  store_grad_rows<D>(stg + 32 * TL::kRowBytes, acc_dv, mul_v, reinterpret_cast<_Float16*>(a.ws + P.dv_off) + wrow0 * D,
-                     L - kw0, lane);
+  _Float16* dk = reinterpret_cast<_Float16*>(a.ws + P.dk_off) + wrow0 * D + part * C;
+  _Float16* dv = reinterpret_cast<_Float16*>(a.ws + P.dv_off) + wrow0 * D + part * C;
+  store_grad_rows<C, D>(stg, acc_dk, mul_k, dk, L - kw0, lane);
+  store_grad_rows<C, D>(stg + 32 * TL::kRowBytes, acc_dv, mul_v, dv, L - kw0, lane);
   if (hi == 0 && k_valid) {
-    reinterpret_cast<float*>(a.ws + P.dk_rec_off)[wrow0 + kr] = rs_k;
-    reinterpret_cast<float*>(a.ws + P.dv_rec_off)[wrow0 + kr] = rs_v;
+    reinterpret_cast<float*>(a.ws + P.dk_rec_off)[(wrow0 + kr) * kParts + part] = rs_k;
+    reinterpret_cast<float*>(a.ws + P.dv_rec_off)[(wrow0 + kr) * kParts + part] = rs_v;
   }
 }
 
@@ -917,6 +922,18 @@ __global__ __launch_bounds__(kThreadsB) void bwd_sum(SumArgs a) {
   store_bf16x8(a.dv + o, sv);
 }
 
+// Items of the launch's busiest XCD: its units' short tiles, and its share of
+// the long ones (see decode_item; XCD 0 has the most of both).
+int64_t items_on_xcd0(const Plan& plan) {
+  int64_t n = 0;
+  for (int i = 0; i < plan.npat; ++i) {
+    const int64_t units = plan.pat[i].units, nt = plan.pat[i].ntiles;
+    const int64_t nlong = nt > kShortTiles ? nt - kShortTiles : 0;
+    n += (units + 7) / 8 * (nt - nlong) + units / 8 * nlong + (units % 8 * nlong + 7) / 8;
+  }
+  return n;
+}
+
 }  // namespace
 
 hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q, const void* k, const void* v,
@@ -1028,7 +1045,19 @@ hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q
       if (delta) hipLaunchKernelGGL(bwd_delta<128>, rgrid, dim3(kThreadsB), 0, stream, da_);
       if (plan.total_items > 0) {
         hipLaunchKernelGGL((delta ? bwd_dq<128, false> : bwd_dq<128, true>), igrid, dim3(kThreadsB), 0, stream, a);
-        hipLaunchKernelGGL(bwd_dkdv_wide<128>, igrid, dim3(kThreadsB), 0, stream, a);
+        // 16 items on an XCD leave half of its 32 CUs without one: run twice,
+        // once per column half, an item's chain is shorter (under a causal mask
+        // also where 128 items fall unevenly: the short ones share their CUs).
+        // Whole call, us, bwd_dkdv_wide -> bwd_dkdv, one pattern: causal, 8
+        // heads, N = 2048 (16 items an XCD) 128 -> 119, 1 head, N = 8192 450 ->
+        // 403, 2 heads (128 items) 451 -> 412, 32 heads, N = 512 49 -> 47; past
+        // the line, 12 heads, N = 2048 132 -> 139, 8 heads, N = 8192 573 -> 646;
+        // not causal, 8 heads, N = 2048 128 -> 118, 2 heads, N = 8192 (19 items
+        // on XCD 0) 454 -> 483.
+        if (items_on_xcd0(plan) <= 16 || (plan.causal && plan.total_items <= 128))
+          hipLaunchKernelGGL(bwd_dkdv<128>, grid_of(2 * plan.launch_items), dim3(kThreadsB), 0, stream, a);
+        else
+          hipLaunchKernelGGL(bwd_dkdv_wide<128>, igrid, dim3(kThreadsB), 0, stream, a);
       }
       hipLaunchKernelGGL(bwd_sum<128>, rgrid, dim3(kThreadsB), 0, stream, sa);
       break;

@@ -81,6 +81,21 @@ def test_backward_all_rows(case):
     note(f"[bwd] {case}: errors dq {errs[0]:.2e} dk {errs[1]:.2e} dv {errs[2]:.2e}")
 
 
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("n", [31, 32, 33, 65, 97, 129])
+def test_backward_d128_one_pass_per_item(n, causal):
+    """D = 128 with more items than CUs (130 heads, 130 items and more of each
+    pattern): dk and dv of all columns at once, where the cases above, of few
+    items, take one column half per workgroup."""
+    H, pats, hs = 130, [(n, 1), (n // 2 + 1, 2)], [0, 7, 129]
+    note(f"[bwd] D128 N={n} H={H} causal={causal}")
+    q, k, v, dout = _inputs(1, n, H, 128, seed=600 + n)
+    grads = _gpu_bwd(q, k, v, dout, pats, causal)
+    refs = oracle.dilated_attention_bwd_ref(*(to64(t) for t in (q, k, v, dout)), pats, causal, heads=hs)
+    for name, g, r in zip(("dq", "dk", "dv"), grads, refs):
+        _check(name, to64(g)[:, :, hs], r[:, :, hs], f"D128 N{n}")
+
+
 def test_backward_n8k_two_heads():
     """The 8K workload's shapes (2 x 8192 x 12 x 64, patterns up to w = 8192),
     every row of heads 0 and 5."""
