@@ -68,8 +68,9 @@ enum {
 typedef struct {
   uint64_t workspace_bytes; /* device memory the caller passes to fwd        */
   int64_t num_work_items;   /* attention work items (pattern, b, h, segment,
-                               query tile of 128 rows, or 64 in float32;
-                               small bf16 launches cut them in two)           */
+                               query tile of 128 rows, or 64 in float32); bf16
+                               launches too small to fill the chip cut each in
+                               two                                            */
   int64_t covered_rows;     /* sum over patterns of kept (b, row, head) rows  */
   double sparse_flops;      /* 4*D per unmasked (query, key) pair, the work of
                                Sec. 2.4 counted exactly                       */
@@ -119,6 +120,12 @@ int dilated_attn_plan(int64_t B, int64_t N, int64_t H, int64_t D,
  * 2^-11 of the row's largest magnitude; the mixture in float32; out rounded
  * once to bf16.  Results are finite whenever every scaled score is finite in
  * float32 and max|v| < 2^95.  DA_F32 computes in float32 throughout.
+ *
+ * The same call gives the same bits every time.  DA_BF16 launches too small to
+ * fill the chip sum each row's keys in two halves (all sizes of the call, B
+ * among them, decide it), so that a sequence run alone and within a larger
+ * batch may differ by the rounding of float32 sums and of bf16 probabilities.
+ * DA_F32 results and the backward's do not depend on the batch.
  */
 int dilated_attn_fwd(const void* q, const void* k, const void* v, void* out,
                      float* lse, int64_t B, int64_t N, int64_t H, int64_t D,

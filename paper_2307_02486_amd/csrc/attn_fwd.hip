@@ -70,7 +70,7 @@ struct SmemBf16 {
 };
 
 // KS = 1: each of the four waves holds 32 query rows and takes every key.
-// KS = 2 (small launches, see launch_attention): two blocks of 32 query rows
+// KS = 2 (small launches, see split_keys): two blocks of 32 query rows
 // times two halves of the keys; the wave of half w takes the 32-key block w of
 // every 64-key tile, and the halves' (max, sum, O) meet in LDS at the end.
 template <int D, bool kBufferLoads, int KS>
@@ -681,7 +681,35 @@ void launch_bf16(bool offsets32, bool split, const dim3& grid, hipStream_t strea
   }
 }
 
-constexpr int64_t kSplitItems = 512;  // see the rule in launch_attention
+// Whether a bf16 launch splits the keys of 64-row items over two waves: the
+// chain of MFMAs of its longest items is half as long, but every key tile is
+// loaded for half as many rows, so that it pays while the items are too few to
+// fill the chip, and the longer the longer their chains.  The items are counted
+// as X = their key tiles altogether / those of the longest, C.  Call, us, 128-row
+// items -> split, one dense pattern:
+//   X = 128 (a CU for each half of an item): D = 64, not causal, C = 4 10.7 ->
+//     10.5, C = 16 18.0 -> 15.5, C = 64 51 -> 48; D = 128, C = 16 26 -> 22;
+//   not causal beyond: C = 8, X = 144 13.1 -> 13.7 (D = 128 18.7 -> 19.6), C = 16
+//     19.2 -> 19.1; from C = 32 on X = 320 still gains at D <= 64 (C = 32 41 -> 39,
+//     C = 64 73 -> 67; X = 384 8 % lost at C = 64, 480 7 %) and X = 224 at D = 128
+//     (46.1 -> 45.2; X = 288 64 -> 72);
+//   causal beyond: C = 8, X = 160 2 % gained (D = 128 2 % lost, X = 225 8 %), C =
+//     16, X = 162 20.4 -> 19.1, C = 32, X = 153 12 % gained and X = 162 5 % lost, C =
+//     64, X = 264 69 -> 61 (D = 128 113 -> 95; X = 280 116 -> 129).  The paper's
+//     five patterns, 12 heads, N = 2048 (C = 32, X = 143): 33.4 -> 30.7.
+bool split_keys(const Plan& plan) {
+  if (plan.dtype != DA_BF16) return false;
+  int64_t longest = 0, total = 0;
+  for (int i = 0; i < plan.npat; ++i) {
+    const PatternPlan& pp = plan.pat[i];
+    const int64_t tiles = (pp.lmax + kBN - 1) / kBN;  // key tiles of the segment's last item
+    longest = std::max(longest, tiles);
+    total += pp.units * (plan.causal ? pp.ntiles * (pp.ntiles - 1) * (kBM / kBN / 2) + tiles : pp.ntiles * tiles);
+  }
+  const int64_t most = plan.causal ? (longest >= 64 ? 264 : longest >= 8 ? 160 : 128)
+                                   : (longest >= 32 ? (plan.D <= 64 ? 320 : 224) : 128);
+  return total <= most * longest;
+}
 
 }  // namespace
 
@@ -697,14 +725,7 @@ hipError_t launch_attention(const Plan& plan, const void* q, const void* k, cons
   a.H = static_cast<int32_t>(plan.H);
   a.causal = plan.causal;
   a.scale_log2 = plan.scale * kLog2e;
-  // A launch of at most 512 items of 128 rows (two per CU) leaves the chip
-  // waiting for the longest items' chains: 64-row items with split keys halve
-  // those.  Attention launch, us, 128-row items -> split: 12 heads of 64, the
-  // paper's five patterns: N = 1024 (204 items) 18.9 -> 15.9, 2048 (396) 30.6
-  // -> 28.4, 3072 (672) 33.2 -> 33.1, 4096 (780) 40.6 -> 43.2; causal dense, 8
-  // heads, N = 8192 (512) 106 -> 92; D = 128, 8 heads, N = 2048 (264) 44 -> 34;
-  // D = 32, B = 2, N = 5003, three patterns (720) 19.3 -> 21.5.
-  const bool split = plan.dtype == DA_BF16 && plan.total_items <= kSplitItems;
+  const bool split = split_keys(plan);
   const int64_t bm = split ? kBM / 2 : plan.block_m;
   auto tiles = [&](const PatternPlan& pp) { return (pp.lmax + bm - 1) / bm; };
   // The patterns of the launch, most query tiles per unit first.

@@ -1,6 +1,6 @@
 """The bf16 forward's two forms: 64-row items whose keys are split over two
-waves (launches of at most 512 items of 128 rows) and 128-row items, each
-against the oracle where it can go wrong.  Bars: those of the bf16 parity tests
+waves (launches too small to fill the chip) and 128-row items, each against
+the oracle where it can go wrong.  Bars: those of the bf16 parity tests
 (2e-2 on out, 1e-2 on lse: bf16 probabilities and outputs of size about 1)."""
 import pytest
 import torch
@@ -83,3 +83,26 @@ def test_scores_far_below_zero(H, causal, D):
     q, k, v = (workloads.make_random((1, 200, H, D), torch.bfloat16, 1.0, 330 + D, "cuda", t) for t in range(3))
     q[..., 1], k[..., 1] = 64.0, -32.0
     compare_full(q, k, v, [(200, 1), (100, 2)], causal, "bf16", tag=f"low H{H} D{D}", heads=[0, H - 1])
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_a_sequence_alone_and_in_a_batch(D):
+    """Float32 gives the same bits; bf16 may take the other form in the batch,
+    whose results differ within the bars both keep to the oracle (2e-2 on out
+    and 1e-2 on lse, twice).  The backward, given the same out and lse, gives
+    the same bits."""
+    from paper_2307_02486_amd import dilated_attn, dilated_attn_bwd
+    note(f"[split] batch D={D}")
+    pats = [(300, 1), (700, 2)]
+    for dtype in (torch.float32, torch.bfloat16):
+        q, k, v, dout = (workloads.make_random((16, 700, 8, D), dtype, 1.0, 340, "cuda", t) for t in range(4))
+        out, lse = dilated_attn(q, k, v, pats)
+        one, l1 = dilated_attn(q[:1], k[:1], v[:1], pats)
+        if dtype == torch.float32:
+            assert torch.equal(one, out[:1]) and torch.equal(l1, lse[:1])
+            continue
+        assert float((one.float() - out[:1].float()).abs().max()) <= 4e-2
+        assert float((l1 - lse[:1]).abs().max()) <= 2e-2
+        grads = dilated_attn_bwd(q, k, v, out, lse, dout, pats)
+        alone = dilated_attn_bwd(q[:1], k[:1], v[:1], out[:1], lse[:1], dout[:1], pats)
+        assert all(torch.equal(a, g[:1]) for a, g in zip(alone, grads))
