@@ -48,22 +48,28 @@ def _pattern_array_cached(pats: tuple):
     return _lib.pattern_array(pats)
 
 
-@functools.lru_cache(maxsize=256)
-def _prepared_cached(entry: str, B: int, N: int, H: int, D: int, patterns: tuple, causal: int, dtype_code: int,
-                     scale: float):
-    pats = _pattern_key(patterns)
-    info = _plan_cached(entry, B, N, H, D, pats, causal, dtype_code, scale)
-    return (max(256, int(info["workspace_bytes"])), *_pattern_array_cached(pats))
+_PREPARED: dict = {}  # calls by their integers, at most 256
 
 
 def _prepared(entry: str, shape, patterns, causal: int, dtype_code: int, scale: float):
-    """(workspace bytes, ctypes pattern array, pattern count) of a call: one
-    look-up by the patterns as given, if they can be a key."""
+    """(workspace bytes, ctypes pattern array, pattern count) of a call.  Entries
+    are kept under the patterns' integers only and found by the patterns as
+    given, that is if these equal the integers at this call: whatever converts
+    to an integer is converted at each call, and nothing given is kept."""
     patterns = tuple(patterns)
     try:
-        return _prepared_cached(entry, *shape, patterns, causal, dtype_code, scale)
+        hit = _PREPARED.get((entry, *shape, patterns, causal, dtype_code, scale))
+        if hit is not None:
+            return hit
     except TypeError:  # patterns given as lists
-        return _prepared_cached(entry, *shape, _pattern_key(patterns), causal, dtype_code, scale)
+        pass
+    pats = _pattern_key(patterns)
+    info = _plan_cached(entry, *shape, pats, causal, dtype_code, scale)
+    hit = (max(256, int(info["workspace_bytes"])), *_pattern_array_cached(pats))
+    if len(_PREPARED) >= 256:
+        _PREPARED.clear()
+    _PREPARED[(entry, *shape, pats, causal, dtype_code, scale)] = hit
+    return hit
 
 
 @functools.lru_cache(maxsize=256)

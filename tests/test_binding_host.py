@@ -1,6 +1,8 @@
 """The binding's per-call look-ups and the layer's choice of the path without
 autograd functions (no GPU needed)."""
 import ctypes
+import gc
+import weakref
 
 import numpy as np
 import pytest
@@ -19,6 +21,20 @@ def test_prepared_takes_every_form_of_patterns(patterns):
         got, arr, n = ops._prepared("dilated_attn_plan", (1, 256, 2, 32), given, 1, 1, 0.0)
         assert got == want and n == 2
         assert [(arr[i].w, arr[i].r) for i in range(n)] == [(64, 1), (128, 2)]
+
+
+def test_prepared_reads_pattern_entries_at_each_call():
+    """Entries that convert to integers are read when the call is made: a tensor
+    entry changed in place is a new pattern, and the look-up keeps no tensor."""
+    w = torch.tensor(64)
+    for value in (64, 128):
+        w.fill_(value)
+        _, arr, n = ops._prepared("dilated_attn_plan", (1, 256, 2, 32), [(w, 1)], 1, 1, 0.0)
+        assert (n, arr[0].w, arr[0].r) == (1, value, 1)
+    held = weakref.ref(w)
+    del w
+    gc.collect()
+    assert held() is None
 
 
 def test_prepared_refuses_what_the_plan_refuses():
