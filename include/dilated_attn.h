@@ -181,7 +181,9 @@ int dilated_attn_fwd_noalloc(const void* q, const void* k, const void* v, void* 
  * the dk/dv kernels' work items, covered_rows, sparse_flops = 10*D per
  * unmasked (query, key) pair (the five products of the derivative),
  * bytes_attn = algorithmic HBM bytes of the two gradient kernels and
- * bytes_combine = those of the delta pass and the gradient-sum kernel.
+ * bytes_combine = those of the gradient-sum kernel and of the delta pass,
+ * which is made only if no pattern has r = 1 (the dq kernel of one that has
+ * reads out and lse itself and writes delta).
  */
 int dilated_attn_bwd_plan(int64_t B, int64_t N, int64_t H, int64_t D,
                           const da_pattern_t* patterns, int64_t num_patterns,

@@ -1021,7 +1021,7 @@ hipError_t launch_backward(const Plan& plan, const BwdLayout& lay, const void* q
   a.delta_pat = -1;
   for (int i = plan.npat - 1; i >= 0; --i)
     if (plan.pat[order[i]].r == 1) a.delta_pat = i;
-  const bool delta = a.delta_pat < 0;
+  const bool delta = lay.delta_pass;
   const dim3 rgrid(static_cast<unsigned>(rblocks));
   const dim3 igrid = grid_of(plan.launch_items);
   switch (plan.D) {

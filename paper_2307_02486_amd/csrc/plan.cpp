@@ -166,13 +166,19 @@ int make_bwd_layout(const Plan& p, BwdLayout* out) {
   const double D = static_cast<double>(p.D), es = 2.0, cov = static_cast<double>(p.covered_rows);
   const double grad_row = D * 2.0 + 4.0 * static_cast<double>(chunks);  // a compact row and its scales
   l.flops = 2.5 * p.sparse_flops;
+  l.delta_pass = true;
+  for (int i = 0; i < p.npat; ++i)
+    if (p.pat[i].r == 1) l.delta_pass = false;
   // each gradient kernel reads the kept q, k, v, dout rows once and the two
-  // per-row scalars; dq writes one compact row, dk/dv two
+  // per-row scalars; dq writes one compact row, dk/dv two.  Without a delta
+  // pass dq reads the kept out rows and lse in place of the scalars, and
+  // writes these once for every row.
   l.bytes_grad = cov * (2.0 * (4.0 * D * es + 8.0) + 3.0 * grad_row);
-  // delta: out, dout and lse of every row read, two scalars written; sum:
-  // the compact gradients read, dq, dk, dv written
-  l.bytes_combine = static_cast<double>(rows_all) * (2.0 * D * es + 4.0 + 8.0 + 3.0 * D * es) +
-                    cov * 3.0 * grad_row;
+  if (!l.delta_pass) l.bytes_grad += cov * (D * es + 4.0 - 8.0) + static_cast<double>(rows_all) * 8.0;
+  // sum: the compact gradients read, dq, dk, dv written; delta: out, dout and
+  // lse of every row read, two scalars written
+  l.bytes_combine = static_cast<double>(rows_all) * 3.0 * D * es + cov * 3.0 * grad_row;
+  if (l.delta_pass) l.bytes_combine += static_cast<double>(rows_all) * (2.0 * D * es + 4.0 + 8.0);
   *out = l;
   return DA_OK;
 }

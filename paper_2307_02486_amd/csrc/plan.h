@@ -85,6 +85,7 @@ struct BwdLayout {
   double flops;          // 10*D per unmasked pair
   double bytes_grad;     // algorithmic HBM bytes of the dq and dk/dv kernels
   double bytes_combine;  // algorithmic HBM bytes of the delta and sum kernels
+  bool delta_pass;       // no pattern keeps every row (r = 1): delta takes a pass of its own
 };
 
 // Columns of a compact gradient row that share one scale.

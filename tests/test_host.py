@@ -191,11 +191,17 @@ def test_profile_window_arguments(lib):
 def test_bwd_plan_accounting():
     """Backward workspace = two [B,H,N] float32 arrays plus, per pattern, three
     fp16 [units][lmax][D] blocks and three float32 [units][lmax][ceil(D/64)]
-    scale blocks, each 256-byte aligned; flops = 10 D per pair."""
+    scale blocks, each 256-byte aligned; flops = 10 D per pair.  Bytes: both
+    gradient kernels read q, k, v, dout of every kept row, dk/dv two scalars
+    beside them, dq the out row and lse if a pattern has r = 1 (it then writes
+    the scalars of every row), else the scalars too, which a pass over out, dout
+    and lse has written; one compact row and its scales out for each of dq, dk
+    and dv, read again by the sum, which writes the gradients."""
     from paper_2307_02486_amd import plan, plan_bwd
     import torch
     for (B, N, H, D, pats) in [(1, 32768, 12, 64, [(2048, 1), (4096, 2), (8192, 4), (16384, 6), (32768, 12)]),
                                (2, 777, 5, 32, [(256, 1), (512, 7), (1000, 9)]),
+                               (2, 777, 5, 64, [(256, 2), (512, 7)]),
                                (1, 513, 17, 128, [(512, 1), (513, 20)])]:
         f = plan(B, N, H, D, pats, True, torch.bfloat16)
         b = plan_bwd(B, N, H, D, pats, True, torch.bfloat16)
@@ -212,6 +218,11 @@ def test_bwd_plan_accounting():
         assert b["sparse_flops"] == pytest.approx(2.5 * f["sparse_flops"], rel=1e-12)
         assert b["covered_rows"] == f["covered_rows"]
         assert b["num_work_items"] == 2 * f["num_work_items"]
+        kept, rows, row = b["covered_rows"], B * N * H, 2 * D
+        compact = 3 * (row + 4 * (-(-D // 64)))
+        own = any(r == 1 for _, r in pats)
+        assert b["bytes_attn"] == kept * (4 * row + 8 + 4 * row + (row + 4 if own else 8) + compact) + own * 8 * rows
+        assert b["bytes_combine"] == kept * compact + rows * 3 * row + (not own) * rows * (2 * row + 4 + 8)
 
 
 def test_bwd_unsupported_and_errors(lib):
