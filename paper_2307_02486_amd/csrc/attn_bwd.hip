@@ -81,20 +81,15 @@ struct SmemTiles {
   __attribute__((aligned(16))) float s1[2][kStepB];   // -delta of the query rows (dk/dv)
 };
 
-// bf16 row slice [16c + 8hi, +8) of a row, as the MFMA operand layout wants,
-// optionally multiplied by `mul` and rounded back to bf16.
+// bf16 row slices [16c + 8hi, +8) of a row, as the MFMA operand layout wants,
+// or zeros.
 template <int KC>
-__device__ inline void load_rowslices(const u16* row, int hi, float mul, bool zero, bf16x8 (&out)[KC]) {
+__device__ inline void load_rowslices(const u16* row, int hi, bool zero, bf16x8 (&out)[KC]) {
   u32x4 raw[KC];
 #pragma unroll
   for (int c = 0; c < KC; ++c) raw[c] = *reinterpret_cast<const u32x4*>(row + 16 * c + 8 * hi);
 #pragma unroll
-  for (int c = 0; c < KC; ++c)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const unsigned bits = zero ? 0u : (raw[c][e >> 1] >> (16 * (e & 1))) << 16;
-      out[c][e] = (__bf16)(__builtin_bit_cast(float, bits) * mul);
-    }
+  for (int c = 0; c < KC; ++c) out[c] = __builtin_bit_cast(bf16x8, zero ? u32x4{0u, 0u, 0u, 0u} : raw[c]);
 }
 
 // Loads of one tile of kRows kept rows (row stride row_step elements, base at
@@ -253,12 +248,12 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dq(BwdArgs a) {
   };
   load_tile(0, 0);
 
-  // Q^T (times scale*log2e) and dO^T operands of this lane's query, its
-  // -lse*log2e and -delta.
+  // Q^T and dO^T operands of this lane's query (as given), its -lse/scale and
+  // -delta.
   const int64_t qoff = (it.row0 + (int64_t)qrow * it.rstride) * D;
   bf16x8 qreg[KC], doreg[KC];
-  load_rowslices<KC>(static_cast<const u16*>(a.q) + qoff, hi, 1.0f, !q_valid, qreg);
-  load_rowslices<KC>(static_cast<const u16*>(a.dout) + qoff, hi, 1.0f, !q_valid, doreg);
+  load_rowslices<KC>(static_cast<const u16*>(a.q) + qoff, hi, !q_valid, qreg);
+  load_rowslices<KC>(static_cast<const u16*>(a.dout) + qoff, hi, !q_valid, doreg);
   const int64_t srow = ((int64_t)it.b * a.H + it.h) * a.N + it.p0 + (int64_t)qrow * P.r;
   // The scores start from -lse/scale where registers allow (D <= 64), and from
   // zero with -lse added beside the scale otherwise.
@@ -473,8 +468,8 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dkdv(BwdArgs a) {
   // K^T and V^T operands of this lane's key (as given).
   const int64_t koff = (it.row0 + (int64_t)krow * it.rstride) * D;
   bf16x8 kreg[KC], vreg[KC];
-  load_rowslices<KC>(static_cast<const u16*>(a.k) + koff, hi, 1.0f, !k_valid, kreg);
-  load_rowslices<KC>(static_cast<const u16*>(a.v) + koff, hi, 1.0f, !k_valid, vreg);
+  load_rowslices<KC>(static_cast<const u16*>(a.k) + koff, hi, !k_valid, kreg);
+  load_rowslices<KC>(static_cast<const u16*>(a.v) + koff, hi, !k_valid, vreg);
   f32x16 acc_dk[DB], acc_dv[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) acc_dk[db] = acc_dv[db] = f32x16{};
@@ -695,7 +690,7 @@ __global__ __launch_bounds__(kThreadsB, 2) void bwd_dkdv_wide(BwdArgs a) {
   // K^T operand of this lane's key (as given).
   const int64_t koff = (it.row0 + (int64_t)krow * it.rstride) * D;
   bf16x8 kreg[KC];
-  load_rowslices<KC>(static_cast<const u16*>(a.k) + koff, hi, 1.0f, !k_valid, kreg);
+  load_rowslices<KC>(static_cast<const u16*>(a.k) + koff, hi, !k_valid, kreg);
   f32x16 acc_dk[DB], acc_dv[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) acc_dk[db] = acc_dv[db] = f32x16{};

@@ -31,7 +31,7 @@ struct AttnArgs {
   const void* k;
   const void* v;
   char* ws;
-  int32_t B, N, H, npat, causal, total_items;
+  int32_t B, N, H, npat, causal;
   float scale_log2;  // softmax scale times log2(e), applied to the fp32 scores
   // The patterns of this launch, ordered by query tiles per unit, most first
   // (the kernels only use a pattern's index to find its record here).
@@ -43,10 +43,7 @@ struct AttnArgs {
 // ---------------------------------------------------------------------------
 constexpr int kThreads = 256;  // four waves of 32 query rows each
 constexpr int kBM = 128;       // query rows per work item (64 with split keys)
-#ifndef DA_KEY_TILE
-#define DA_KEY_TILE 64
-#endif
-constexpr int kBN = DA_KEY_TILE;  // keys per K/V tile
+constexpr int kBN = 64;        // keys per K/V tile
 // Online softmax without a per-tile row max.  Each row's reference max m is
 // the true max of its first key tile; later tiles exponentiate S - m directly
 // and the row's reference is moved only afterwards, from the tile's row sums:
@@ -755,7 +752,6 @@ hipError_t launch_attention(const Plan& plan, const void* q, const void* k, cons
       pa = PatArgs{1, 1, 1, 1, 1, 0, 0, 0};
     }
   }
-  a.total_items = static_cast<int32_t>(items);
   if (items == 0) return hipSuccess;
   const dim3 grid = grid_of(launch);
   if (plan.dtype == DA_BF16) {
