@@ -280,7 +280,10 @@ def xpos(x: torch.Tensor, sign: int, transpose: bool = False, center: int | None
     if x.dim() != 4 or not x.is_contiguous():
         raise ValueError("x must be a contiguous [B, N, H, D] tensor")
     B, N, H, D = x.shape
-    out = torch.empty_like(x) if out is None else out
+    owned = []
+    if out is None:
+        out = torch.empty_like(x)
+        owned.append(out)
     if out.shape != x.shape or out.dtype != x.dtype or out.device != x.device or not out.is_contiguous():
         raise ValueError("out must be a contiguous tensor like x")
     raw = _raw_stream(x.device) if stream is None else stream.cuda_stream
@@ -289,6 +292,7 @@ def xpos(x: torch.Tensor, sign: int, transpose: bool = False, center: int | None
                                float(scale_base), _dtype_code(x.dtype), raw)
     if rc != 0:
         raise _lib.DilatedAttnError(rc, lib)
+    _stream_use(stream, owned)
     return out
 
 
@@ -307,17 +311,21 @@ def wgrad(dy: torch.Tensor, x: torch.Tensor, out: torch.Tensor | None = None, bi
     K, M = dy.shape
     N = x.shape[1]
     need = _workspace_bytes("dilated_attn_wgrad_workspace", K, M, N)
-    out = torch.empty((M, N), dtype=dy.dtype, device=dy.device) if out is None else out
+    owned = []
+    if out is None:
+        out = torch.empty((M, N), dtype=dy.dtype, device=dy.device)
+        owned.append(out)
     if out.shape != (M, N) or out.dtype != dy.dtype or out.device != dy.device or not out.is_contiguous():
         raise ValueError("out must be a contiguous [M, N] tensor of dy's dtype")
     ws = torch.empty(max(need, 16), dtype=torch.uint8, device=dy.device)
     raw = _raw_stream(dy.device) if stream is None else stream.cuda_stream
     db = torch.empty((M,), dtype=dy.dtype, device=dy.device) if bias_grad else None
+    owned += [ws, db] if bias_grad else [ws]
     rc = lib.dilated_attn_wgrad(dy.data_ptr(), x.data_ptr(), out.data_ptr(), db.data_ptr() if bias_grad else None,
                                 K, M, N, _dtype_code(dy.dtype), ws.data_ptr(), need, raw)
     if rc != 0:
         raise _lib.DilatedAttnError(rc, lib)
-    _stream_use(stream, [ws])
+    _stream_use(stream, owned)
     return (out, db) if bias_grad else out
 
 
@@ -347,6 +355,7 @@ def layer_norm(x: torch.Tensor, weight: torch.Tensor, bias: torch.Tensor, eps: f
                                         _dtype_code(x.dtype), raw)
     if rc != 0:
         raise _lib.DilatedAttnError(rc, lib)
+    _stream_use(stream, [y, mean, rstd])
     return y, mean, rstd
 
 
@@ -379,5 +388,5 @@ def layer_norm_bwd(dy: torch.Tensor, x: torch.Tensor, weight: torch.Tensor, mean
                                         _dtype_code(x.dtype), ws.data_ptr(), need, raw)
     if rc != 0:
         raise _lib.DilatedAttnError(rc, lib)
-    _stream_use(stream, [ws])
+    _stream_use(stream, [ws, dx, dw, db])
     return dx, dw, db

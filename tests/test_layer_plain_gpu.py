@@ -60,3 +60,18 @@ def test_qkv_gradients_match_single_projections(dtype, E, frozen):
             assert float((g.float() - w.float()).abs().max()) <= tol
         else:
             assert torch.equal(g, w)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=str)
+@pytest.mark.parametrize("mode", [torch.no_grad, torch.inference_mode, torch.enable_grad])
+def test_a_trace_replays_on_new_inputs(dtype, mode):
+    """torch.jit.trace keeps the kernels' calls whatever the gradient mode."""
+    from paper_2307_02486_amd.layer import LongNetAttention
+    note(f"[plain] trace {dtype} {mode.__name__}")
+    torch.manual_seed(2)
+    layer = LongNetAttention(128, 2, [(64, 1), (128, 2)], device="cuda", dtype=dtype)
+    x0, x1 = (workloads.make_random((2, 128, 128), dtype, 1.0, 62, "cuda", i) for i in range(2))
+    with mode():
+        traced = torch.jit.trace(layer, x0, check_trace=False)
+    with torch.no_grad():
+        assert torch.equal(traced(x1), layer(x1)) and torch.equal(traced(x0), layer(x0))

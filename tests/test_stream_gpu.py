@@ -24,9 +24,11 @@ def test_raw_stream_is_the_current_one():
     assert ops._raw_stream(dev) == torch.cuda.current_stream(dev).cuda_stream
 
 
-def test_a_given_stream_gives_the_same_bits():
+def test_a_given_stream_gives_the_same_bits(monkeypatch):
     """Each entry point on a stream that is not the current one (its inputs made
-    and waited for before), against the current one."""
+    and waited for before), against the current one.  Every tensor it returns
+    is recorded for that stream: the binding allocated it on the current one."""
+    from paper_2307_02486_amd import ops
     from paper_2307_02486_amd import dilated_attn, dilated_attn_bwd, layer_norm, layer_norm_bwd, wgrad, xpos
     note("[stream] given stream")
     q, k, v, dout = (workloads.make_random((1, 300, 4, 64), torch.bfloat16, 1.0, 90, "cuda", t) for t in range(4))
@@ -47,6 +49,15 @@ def test_a_given_stream_gives_the_same_bits():
     want = [t for ts in calls(None) for t in ts]
     torch.cuda.synchronize()
     side = torch.cuda.Stream()
+    owned = []
+    record = ops._stream_use
+
+    def use(stream, tensors):
+        owned.extend(t.data_ptr() for t in tensors)
+        record(stream, tensors)
+
+    monkeypatch.setattr(ops, "_stream_use", use)
     got = [t for ts in calls(side) for t in ts]
     torch.cuda.synchronize()
+    assert {t.data_ptr() for t in got} <= set(owned)
     assert all(torch.equal(a, b) for a, b in zip(got, want))
