@@ -119,7 +119,8 @@ int dilated_attn_plan(int64_t B, int64_t N, int64_t H, int64_t D,
  * kept in the workspace as fp16 divided by a power of two per row, within
  * 2^-11 of the row's largest magnitude; the mixture in float32; out rounded
  * once to bf16.  Results are finite whenever every scaled score is finite in
- * float32 and max|v| < 2^95.  DA_F32 computes in float32 throughout.
+ * float32 and max|v| < 2^95 (a score that overflows to minus infinity beside a
+ * finite one has no weight).  DA_F32 computes in float32 throughout.
  *
  * The same call gives the same bits every time.  DA_BF16 launches too small to
  * fill the chip sum each row's keys in two halves (all sizes of the call, B

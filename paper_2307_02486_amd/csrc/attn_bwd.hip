@@ -208,9 +208,10 @@ __global__ __launch_bounds__(kThreadsB) void bwd_delta(DeltaArgs a) {
 // bwd_dq: one work item = 128 query rows of one sparsified segment, all head-dim
 // columns.  Three waves per SIMD, two at D = 128, where the scores start from
 // zero and -lse enters with the scale in one FMA (the 16 registers this frees
-// hold row slices in flight: 250 VGPRs).  D = 128, B = 1, N = 32768, H = 16,
-// patterns (2048, 1), (8192, 2), (32768, 4): 1095 us, against 1877 us when the
-// items ran once per 64-column half (40 instead of 24 MFMAs per block).
+// hold row slices in flight: 252 VGPRs; MFMA 56 % busy).  D = 128, B = 1, N =
+// 32768, H = 16, patterns (2048, 1), (8192, 2), (32768, 4): 1103 us, against 1904
+// us when the items ran once per 64-column half (40 instead of 24 MFMAs per
+// block) and a pass of its own formed delta.
 // ---------------------------------------------------------------------------
 // kDelta: delta is formed here, and the items of pattern delta_pat write it;
 // otherwise bwd_delta has written it.
@@ -611,11 +612,11 @@ __global__ __launch_bounds__(kThreadsB) void bwd_dkdv(BwdArgs a) {
 // and 128 columns alone are 128 registers, K and V operands 64, scores and dP
 // 32.  The V operands are therefore read from LDS (the item's 128 V rows stay
 // there; dP's B operand costs 8 more 16-byte reads per 32-query block, with
-// the LDS 39 % busy), and Q/dO tiles are 32 rows, so that two workgroups share
-// a CU (66 KB of LDS, 252 VGPRs, nothing spilled).  Bound by the matrix cores
-// and the softmax's vector work, which overlap only in part (MFMA 51 % busy).
+// the LDS 44 % busy), and Q/dO tiles are 32 rows, so that two workgroups share
+// a CU (66 KB of LDS, 256 VGPRs, nothing spilled).  Bound by the matrix cores
+// and the softmax's vector work, which overlap only in part (MFMA 52 % busy).
 // At B = 1, N = 32768, H = 16, patterns (2048, 1), (8192, 2), (32768, 4):
-// 1574 us, against 2330 us when every item ran once per 64-column half and
+// 1563 us, against 2392 us when every item ran once per 64-column half and
 // formed the scores and dP twice (48 instead of 32 MFMAs per 32 x 32 block).
 // One wave per SIMD with 512 registers was not built further: the compiler
 // copies the operands it keeps in accumulation registers before every MFMA.

@@ -16,10 +16,10 @@
 // result does not depend on scheduling).
 // The row loop was bound by its vector work and the latency of its two wave
 // sums (LDS lane exchanges, 12 in a chain); with full lanes, sums by DPP, no
-// lane masks in the sums and one resident round of workgroups the 32768 x 768
-// backward takes 25.7 us instead of 34.0 (5.9 TB/s), 28 instead of 48 on data
-// that no cache holds, and its reduction 4 us in one kernel instead of 8.5 in
-// two.
+// lane masks in the sums (but in the last chunks) and one resident round of
+// workgroups the 32768 x 768 backward takes 25.7 us instead of 34.0 (5.9 TB/s),
+// 28 instead of 48 on data that no cache holds, and its reduction 4 us in one
+// kernel instead of 8.5 in two.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
