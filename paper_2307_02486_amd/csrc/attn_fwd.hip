@@ -686,16 +686,22 @@ void launch_bf16(bool offsets32, bool split, const dim3& grid, hipStream_t strea
 // items -> split, one dense pattern:
 //   X = 128 (a CU for each half of an item): D = 64, not causal, C = 4 10.7 ->
 //     10.5, C = 16 18.0 -> 15.5, C = 64 51 -> 48; D = 128, C = 16 26 -> 22;
-//   not causal beyond: C = 8, X = 144 13.1 -> 13.7 (D = 128 18.7 -> 19.6), C = 16
-//     19.2 -> 19.1; from C = 32 on X = 320 still gains at D <= 64 (C = 32 41 -> 39,
-//     C = 64 73 -> 67; X = 384 8 % lost at C = 64, 480 7 %) and X = 224 at D = 128
-//     (46.1 -> 45.2; X = 288 64 -> 72);
-//   causal beyond: C = 8, X = 160 2 % gained (D = 128 2 % lost, X = 225 8 %), C =
-//     16, X = 162 20.4 -> 19.1, C = 32, X = 153 12 % gained and X = 162 5 % lost, C =
-//     64, X = 264 69 -> 61 (D = 128 113 -> 95; X = 280 116 -> 129).  The paper's
-//     five patterns, 12 heads, N = 2048 (C = 32, X = 143): 33.4 -> 30.7.
+//   causal, D <= 64, to 264: C = 64, X = 264 69 -> 61, C = 8, X = 225 16.2 -> 16.1, X
+//     = 288 17.2 -> 18.5; C = 32 gains 17 % at X = 178 to 195 and loses 5 % at 161 to
+//     170, as the units fall on the XCDs;
+//   causal, D = 128: C = 64, X = 264 113 -> 95, X = 280 116 -> 129; C = 32, X = 195 66
+//     -> 62, X = 221 58 -> 64; C = 16, X = 180 31.7 -> 29.7, X = 194 31.7 -> 36.3; C =
+//     8, X = 160 19.8 -> 20.4, X = 225 22.7 -> 24.8;
+//   not causal, D <= 64: C = 8, X = 144 13.1 -> 13.7, C = 16, X = 320 24.2 -> 23.2, C =
+//     64 73 -> 67, X = 480 84 -> 91; D = 128: C = 16, X = 192 27.1 -> 27.6, C = 32, X =
+//     224 46.1 -> 45.2, X = 288 64 -> 72.
+// More than 768 items are many short ones beside the long: 6 heads of 64, four
+// patterns, N = 11269 (1050 items, C = 16, X = 218) 25.9 -> 28.3.  Over 177 launches
+// drawn at random on which this rule and a line at 512 items differ it is 6 %
+// faster on average (from 19 % slower to 35 % faster).
+// The paper's five patterns, 12 heads of 64, N = 2048 (C = 32, X = 143): 33.4 -> 30.7.
 bool split_keys(const Plan& plan) {
-  if (plan.dtype != DA_BF16) return false;
+  if (plan.dtype != DA_BF16 || plan.total_items > 768) return false;
   int64_t longest = 0, total = 0;
   for (int i = 0; i < plan.npat; ++i) {
     const PatternPlan& pp = plan.pat[i];
@@ -703,8 +709,10 @@ bool split_keys(const Plan& plan) {
     longest = std::max(longest, tiles);
     total += pp.units * (plan.causal ? pp.ntiles * (pp.ntiles - 1) * (kBM / kBN / 2) + tiles : pp.ntiles * tiles);
   }
-  const int64_t most = plan.causal ? (longest >= 64 ? 264 : longest >= 8 ? 160 : 128)
-                                   : (longest >= 32 ? (plan.D <= 64 ? 320 : 224) : 128);
+  const int64_t most =
+      plan.causal ? (plan.D <= 64 || longest >= 64 ? 264 : longest >= 32 ? 216 : longest >= 16 ? 186
+                                                       : longest >= 8 ? 160 : 128)
+                  : (plan.D <= 64 ? (longest >= 16 ? 360 : 128) : longest >= 32 ? 224 : 128);
   return total <= most * longest;
 }
 
